@@ -94,6 +94,30 @@ struct CoarseSplit {
 // by Gauss-Jordan, 1 / a_dd on D; iwork: 2 nf ints; status[0] = 0 ok, else
 // 1 + failing step (the steps of D follow the nf of F)
 constexpr int kMaxCoarse = 6144;
+// the check of D's diagonal entries alone (nf: the steps that come before them)
+void launch_coarse_diagonal(const CoarseSplit &cs, int nf, int *status, hipStream_t st);
+// The free block ordered so that it is banded (band_order), for its LU
+// elimination: before panel p (16 columns) the rows [0, hi[p]) may be nonzero
+// in it, their columns end below cend[p]; at most nslot rows (a multiple of
+// 16, <= kLuBandSlots) wait for their pivot at a time.  rpos/cpos: the places
+// of each dof's row and column, -1 in D; rowdof/coldof: the dofs of the
+// ordered rows and columns.  Work: perm (n ints) and plo (one int per panel)
+// for the pivot rows and where their factors begin, scale ((kEquilSteps + 1)
+// n0 ints) for the equilibration.
+struct BandView {
+  int n = 0, nslot = 0;
+  const int *hi = nullptr, *cend = nullptr, *rpos = nullptr, *cpos = nullptr, *rowdof = nullptr, *coldof = nullptr;
+  int *perm = nullptr, *plo = nullptr, *scale = nullptr;
+};
+constexpr int kEquilSteps = 4;
+constexpr int kLuBandSlots = 320;    // waiting rows that one wave holds without spilling (5 a lane)
+constexpr int kLuBandMax = 2560;     // largest ordered block (20 panels a wave in k_lu_band_rows)
+// once before the first lu_coarse (which may be captured into a graph)
+void lu_coarse_prepare();
+// as gj_coarse, from the operator itself; A: work of n rows of ld doubles (a
+// multiple of 16)
+void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &J, const CoarseSplit &cs, double *C0,
+               int *status, hipStream_t st);
 void launch_fill_i32(int *x, int n, int v, hipStream_t st);
 // x[i] = i for i < n
 void launch_iota_i32(int *x, int n, hipStream_t st);

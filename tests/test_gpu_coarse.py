@@ -164,3 +164,62 @@ def test_coarsest_zero_diagonal_only_dof_is_reported():
     with pytest.raises(FsiError) as e:
         MG(OneLevel(A), precision="fp64")
     assert "coarsest" in str(e.value)
+
+
+def banded_saddle(n, half, seed):
+    """n x n saddle-point matrix whose entries lie within `half` of the
+    diagonal: every fifth dof has a zero diagonal (a pressure-like dof, which
+    needs row pivoting) and couples to its neighbours only; rows and columns
+    then shuffled by one random permutation."""
+    rng = np.random.default_rng(seed)
+    rows, cols, vals = [], [], []
+    for i in range(n):
+        for j in range(max(0, i - half), min(n, i + half + 1)):
+            pi, pj = i % 5 == 4, j % 5 == 4
+            if i == j:
+                v = 0.0 if pi else 8.0 + rng.uniform()
+            elif pi and pj:
+                continue
+            elif pi or pj:
+                if abs(i - j) > 4 and rng.uniform() > 0.2:
+                    continue
+                v = rng.choice([-1.0, 1.0]) * rng.uniform(0.5, 1.5)
+            else:
+                if rng.uniform() > 8.0 / half:
+                    continue
+                v = rng.uniform(-1.0, 1.0)
+            rows.append(i)
+            cols.append(j)
+            vals.append(v)
+    A = sp.csr_matrix((vals, (rows, cols)), shape=(n, n))
+    p = rng.permutation(n)
+    A = A[p][:, p].tocsr()
+    A.sort_indices()
+    return A
+
+
+# the banded elimination: sizes around one and several 16-column panels and
+# the kernels' largest (9 and 20 panels a wave), bands that keep 1 to 5 rows a
+# lane waiting, and one beyond them (the Gauss-Jordan chain).  The error bound
+# is 1e2 eps cond, with cond from numpy.
+@pytest.mark.parametrize("n,half", [(15, 4), (16, 5), (17, 5), (130, 20), (511, 40), (1152, 60), (1153, 100),
+                                    (700, 128), (900, 150), (1000, 190), (2560, 30), (2561, 30)])
+def test_coarsest_banded_elimination(n, half):
+    import torch
+
+    from paper_1709_05660_amd import MG
+    A = banded_saddle(n, half, 40 + n)
+    D = A.toarray()
+    mg = MG(OneLevel(A), precision="fp64")
+    rng = np.random.default_rng(n)
+    B = rng.standard_normal((3, n))
+    Y = [mg.apply(0, 5, torch.as_tensor(b, device="cuda")).cpu().numpy() for b in B]
+    mg.refactor()
+    again = mg.apply(0, 5, torch.as_tensor(B[0], device="cuda")).cpu().numpy()
+    mg.close()
+    ref = np.linalg.solve(D, B.T).T
+    tol = 1e2 * np.finfo(float).eps * np.linalg.cond(D)
+    err = max(np.linalg.norm(y - x) / np.linalg.norm(x) for y, x in zip(Y, ref))
+    _say("banded coarse", n, half, "rel err", err, "tol", tol)
+    assert err <= tol
+    assert np.array_equal(again, Y[0])
