@@ -82,11 +82,11 @@ def measured_traffic(path=TRAFFIC_PROFILE, digest=ras_kernel_digest, variant=Non
 GJ_VARIANTS = {1: ("NB16 x 256, FP64", 16, 8), 2: ("NB16 x 512, FP64", 16, 8),
                3: ("NB32 x 512, LDS panel, FP64", 32, 8), 4: ("wide panel from the block, FP64", 32, 8),
                5: ("NB24 x 512, LDS panel, FP64", 24, 8),
-               6: ("NB32 pairs x 512, FP64", 64, 8),
+               6: ("NB32 pairs x 512, FP64", 64, 8), 7: ("LU, 16-column panels, FP64", 16, 8),
                11: ("NB64 x 512, FP32", 64, 4),
                12: ("NB32 x 512, FP32", 32, 4), 13: ("NB32 x 256 (2 rows/thread), FP32", 32, 4),
                14: ("NB32 x 512 (2 rows/thread), FP32", 32, 4), 15: ("NB48 x 512 (2 rows/thread), FP32", 48, 4),
-               16: ("NB32 pairs x 512, FP32", 64, 4)}
+               16: ("NB32 pairs x 512, FP32", 64, 4), 17: ("LU, 16-column panels, FP32", 16, 4)}
 
 
 _TUNING_DB = None
@@ -537,18 +537,21 @@ def gpu_leg(args):
                                   sum(mg.level_info(l)["npatch"] for l in range(1, p.nlevels)))
         variant = next((v for k, v in out["autotune_choices"].get("gj_variant", {}).items()
                         if k.startswith(gj_key)), None)
-        vid = next((k for k, v in GJ_VARIANTS.items() if v[0] == variant), 3)
+        vid = next((k for k, v in GJ_VARIANTS.items() if v[0] == variant), 7)
+        kernel = {6: "k_gj_paired<double> (Gauss-Jordan", 7: "k_lu_blocks<double> + k_lu_rows<double> (LU"}.get(
+            vid, "k_gj_batched<double> (Gauss-Jordan")
         nb, wsize = GJ_VARIANTS[vid][1], GJ_VARIANTS[vid][2]
         gj_tflops = lu_flops / (gj_avg_ms * 1e-3) / 1e12 if gcnt else 0.0
         out["roofline"] = {
-            "bound": "mfma", "kernel": ("k_gj_paired<double>" if vid == 6 else "k_gj_batched<double>") +
-                                      " (Gauss-Jordan inverse of all 336 Schwarz blocks, FP64 matrix cores)",
+            "bound": "mfma", "kernel": kernel + " inverse of all 336 Schwarz blocks, FP64 matrix cores)",
             "achieved": round(gj_tflops, 3), "peak": 78.6, "unit": "TFLOP/s",
             "frac": round(gj_tflops / 78.6, 4), "traffic": measured_traffic(GJ_TRAFFIC_PROFILE, gj_kernel_digest, vid),
             "flops_per_launch": lu_flops, "flop_count": "2/3 sum m_k^3 (LU-equivalent work of the local solves)",
             "gauss_jordan_flops_per_launch": gj_flops,
             "frac_on_gauss_jordan_flops": round(gj_flops / (gj_avg_ms * 1e-3) / 1e12 / 78.6, 4) if gcnt else None,
-            "traffic_model_bytes": int(2 * wsize * m3 / nb), "variant": variant,
+            # elimination: every entry read and written once per panel (LU: the
+            # entries not yet eliminated, m^3 / 3 over the panels)
+            "traffic_model_bytes": int(2 * wsize * m3 / nb / (3 if vid == 7 else 1)), "variant": variant,
             "avg_launch_us": round(gj_avg_ms * 1e3, 2), "launches": gcnt,
             "share_of_step": round(gj_avg_ms / out["ms_per_step"], 3)}
         avg_ms = kms / max(cnt, 1)

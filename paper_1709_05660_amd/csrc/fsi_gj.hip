@@ -207,7 +207,7 @@ __global__ __launch_bounds__(NT) void k_gj_batched(T *__restrict__ blocks,
   const int *list = sched + gridDim.x + 1;
   for (int t = sched[blockIdx.x]; t < sched[blockIdx.x + 1]; ++t) {
     const int k = list[t];
-    const int m = pm[k];
+    const int m = pm[k], ld = block_ld(m);
     T *A = blocks + boff[k];
     int *perm = perm_all + poff[k];
     for (int i = tid; i < m; i += NT) s_used[i] = -1;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(NT) void k_gj_batched(T *__restrict__ blocks,
       for (int q = 0; q < R; ++q) {
         const int i = tid + q * NT;
         stp[q] = i < m ? s_used[i] : kNoRow;
-        const T *row = A + min(i, m - 1) * m + p0;
+        const T *row = A + min(i, m - 1) * ld + p0;
 #pragma unroll
         for (int c = 0; c < NB; ++c) v[q][c] = row[c];
       }
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(NT) void k_gj_batched(T *__restrict__ blocks,
         if (i < m) {
 #pragma unroll
           for (int c = 0; c < NB; ++c) {
-            if (c < w) A[i * m + p0 + c] = v[q][c];
+            if (c < w) A[i * ld + p0 + c] = v[q][c];
             if constexpr (!GPC) PC[i * PS + c] = v[q][c];
           }
           if (stp[q] >= p0) s_used[i] = (short)stp[q];
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(NT) void k_gj_batched(T *__restrict__ blocks,
         // X: clamped loads issued together, zeroed outside the panel
         T bx[KC];
 #pragma unroll
-        for (int kk = 0; kk < KC; ++kk) bx[kk] = A[sh.piv[min(kk * 4 + kq, w - 1)] * m + j];
+        for (int kk = 0; kk < KC; ++kk) bx[kk] = A[sh.piv[min(kk * 4 + kq, w - 1)] * ld + j];
 #pragma unroll
         for (int kk = 0; kk < KC; ++kk)
           if (!(colok && kk * 4 + kq < w)) bx[kk] = 0;
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(NT) void k_gj_batched(T *__restrict__ blocks,
         auto load_tile = [&](int rt) {
           acc c;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) c[r] = A[min(rt * 16 + MM::row(r, kq), m - 1) * m + j];
+          for (int r = 0; r < 4; ++r) c[r] = A[min(rt * 16 + MM::row(r, kq), m - 1) * ld + j];
           return c;
         };
         acc ring[kPrefetch];
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(NT) void k_gj_batched(T *__restrict__ blocks,
               for (int kk = 0; kk < KC; ++kk) {
                 if constexpr (GPC) {
                   // clamped to the panel's last column, zeroed beyond it
-                  const T x = A[min(ia, m - 1) * m + p0 + min(kk * 4 + kq, w - 1)];
+                  const T x = A[min(ia, m - 1) * ld + p0 + min(kk * 4 + kq, w - 1)];
                   a[kk] = kk * 4 + kq < w ? x : (T)0;
                 } else {
                   a[kk] = PC[min(ia, m - 1) * PS + kk * 4 + kq];
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(NT) void k_gj_batched(T *__restrict__ blocks,
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
                 const int i = rt * 16 + MM::row(r, kq);
-                if (colok && i < m) A[i * m + j] = c[r];
+                if (colok && i < m) A[i * ld + j] = c[r];
               }
             }
           }
@@ -344,6 +344,7 @@ __device__ __forceinline__ void gj_apply_rows(T *__restrict__ A, int m, int kb, 
   typedef Mfma16<T> MM;
   typedef typename MM::acc acc;
   constexpr int NW = NT / 64, NCT = CW / 16, KR = 4 * KCX, XE = (KR * CW + NT - 1) / NT;
+  const int ld = block_ld(m);
   static_assert(RT * KCX <= 64, "the panel rows of a wave's tiles must fit in registers");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int jl = lane & 15, kq = lane >> 4;
@@ -359,7 +360,7 @@ __device__ __forceinline__ void gj_apply_rows(T *__restrict__ A, int m, int kb, 
     const int ia = min(rt * 16 + jl, m - 1);
 #pragma unroll
     for (int kk = 0; kk < KCX; ++kk) {
-      const T x = A[ia * m + kb + min(kk * 4 + kq, kw - 1)];
+      const T x = A[ia * ld + kb + min(kk * 4 + kq, kw - 1)];
       ah[u][kk] = (rt * 16 + jl < m && kk * 4 + kq < kw) ? x : (T)0;
     }
 #pragma unroll
@@ -375,7 +376,7 @@ __device__ __forceinline__ void gj_apply_rows(T *__restrict__ A, int m, int kb, 
 #pragma unroll
     for (int x = 0; x < XE; ++x) {
       const int e = tid + x * NT, t = e / CW, q = q0 + e % CW;
-      const T v = A[xrows[min(t, kw - 1)] * m + col(min(q, mp - 1))];
+      const T v = A[xrows[min(t, kw - 1)] * ld + col(min(q, mp - 1))];
       xv[x] = (e < KR * CW && t < kw && q < mp) ? v : (T)0;
     }
   };
@@ -409,7 +410,7 @@ __device__ __forceinline__ void gj_apply_rows(T *__restrict__ A, int m, int kb, 
       for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          c[u][ct][r] = A[min((wave + NW * u) * 16 + MM::row(r, kq), m - 1) * m + jc[ct]];
+          c[u][ct][r] = A[min((wave + NW * u) * 16 + MM::row(r, kq), m - 1) * ld + jc[ct]];
     // the next chunk's X: its columns are not touched by this chunk
     const bool more = q0 + CW < mp;
     T xv[XE];
@@ -429,7 +430,7 @@ __device__ __forceinline__ void gj_apply_rows(T *__restrict__ A, int m, int kb, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int i = (wave + NW * u) * 16 + MM::row(r, kq);
-          if (cok[ct] && i < m) A[i * m + jc[ct]] = cc[r];
+          if (cok[ct] && i < m) A[i * ld + jc[ct]] = cc[r];
         }
       }
     }
@@ -461,7 +462,7 @@ __global__ __launch_bounds__(NT) void k_gj_paired(T *__restrict__ blocks, const 
   const int *list = sched + gridDim.x + 1;
   for (int t = sched[blockIdx.x]; t < sched[blockIdx.x + 1]; ++t) {
     const int k = list[t];
-    const int m = pm[k];
+    const int m = pm[k], ld = block_ld(m);
     T *A = blocks + boff[k];
     int *perm = perm_all + poff[k];
     for (int i = tid; i < m; i += NT) s_used[i] = -1;
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(NT) void k_gj_paired(T *__restrict__ blocks, const 
         for (int q = 0; q < R; ++q) {
           const int i = tid + q * NT;
           stp[q] = i < m ? s_used[i] : kNoRow;
-          const T *row = A + min(i, m - 1) * m + p0;
+          const T *row = A + min(i, m - 1) * ld + p0;
 #pragma unroll
           for (int c = 0; c < NB; ++c) v[q][c] = row[c];
         }
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(NT) void k_gj_paired(T *__restrict__ blocks, const 
           if (i < m) {
 #pragma unroll
             for (int c = 0; c < NB; ++c)
-              if (c < w) A[i * m + p0 + c] = v[q][c];
+              if (c < w) A[i * ld + p0 + c] = v[q][c];
             if (stp[q] >= p0) s_used[i] = (short)stp[q];
           }
         }
@@ -1126,7 +1127,7 @@ void launch_iota_i32(int *x, int n, hipStream_t st) {
 template <typename TS>
 __global__ void k_copy_block(const TS *__restrict__ src, int m, double *__restrict__ dst, int64_t ld) {
   const int j = blockIdx.x * 256 + threadIdx.x, i = blockIdx.y;
-  if (j < m) dst[(int64_t)i * ld + j] = (double)src[(int64_t)i * m + j];
+  if (j < m) dst[(int64_t)i * ld + j] = (double)src[(int64_t)i * block_ld(m) + j];
 }
 template <typename TS>
 void launch_copy_block(const TS *src, int m, double *dst, int64_t ld, hipStream_t st) {

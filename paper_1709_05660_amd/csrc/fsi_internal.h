@@ -56,6 +56,7 @@ struct Level {
   int64_t woff16_total = 0;
   // block extraction map (launch_extract_map): nslots (entry, position) pairs
   int64_t ext_nslots = 0;
+  int *row_exp = nullptr;   // exponents of J's rows as scaled for the extraction of the blocks
   int *d_ext_src = nullptr, *d_ext_dst = nullptr;
   int64_t *d_ext_slot_off = nullptr;
   // solid blocks apart (solid_precision / refine_sweeps): owned rows in FP32
@@ -200,6 +201,9 @@ struct MG {
   int gj_grid = 0;        // its workgroups, and their block lists (gj_schedule)
   int *gj_sched = nullptr;
   std::vector<int> h_all_pm;   // block sizes of all levels, in the batched order
+  int *lu_order = nullptr;     // the blocks of the batched inversions, largest first (lu_nblk)
+  double *scaled_val = nullptr;   // a level's scaled operator values while its blocks are extracted (setup scratch)
+  int lu_nblk = 0;
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipGraphExec_t coarse_graph = nullptr;   // the coarsest inversion's launch chain, replayed per refactor

@@ -12,6 +12,11 @@ constexpr int kWave = 64;
 constexpr int kMaxPatch = 800;      // largest Schwarz block of the batched inversion, ILU and refinement
 constexpr int kMaxLargePatch = 6144;   // larger blocks: one Gauss-Jordan chain each (equal to kMaxCoarse)
 
+// Row stride of a dense block in the setup scratch: the blocks of the batched
+// inversions have rows of a multiple of 16 entries (whole aligned 16-column
+// tiles; the padding stays zero until the inversion), larger ones are packed.
+__host__ __device__ __forceinline__ constexpr int block_ld(int m) { return m <= kMaxPatch ? (m + 15) / 16 * 16 : m; }
+
 // CSR on the device: int32 offsets and columns (sizes checked at upload).
 template <typename T>
 struct CsrView {
@@ -38,10 +43,8 @@ void launch_extract_map(const CsrView<double> &J, const int *pm, const int64_t *
                         int *src, int *dst, hipStream_t st);
 // B_k = J[I_k, I_k] through the map (blocks zero-filled beforehand), in
 // FP64 or rounded to FP32
-void launch_extract(const double *val, int64_t nslots, const int *src, const int *dst,
-                    double *blocks, hipStream_t st);
-void launch_extract(const double *val, int64_t nslots, const int *src, const int *dst,
-                    float *blocks, hipStream_t st);
+template <typename TV, typename TB>
+void launch_extract(const TV *val, int64_t nslots, const int *src, const int *dst, TB *blocks, hipStream_t st);
 // Gauss-Jordan inverse of every block, one workgroup per block (m <= 1024),
 // rows never exchanged: Binv[i][c] = S[perm[i]][used[c]] with S left in the
 // block and perm/used at poff[k]; status[k] = 0 ok, else 1 + failing step
@@ -56,10 +59,10 @@ void launch_extract(const double *val, int64_t nslots, const int *src, const int
 // (one row per thread) factored in turn, the rest of the block updated once
 // per pair.
 enum GjVariant { kGjAuto = 0, kGj16x256 = 1, kGj16x512 = 2, kGj32x512 = 3, kGjWideG = 4, kGj24x512 = 5,
-                 kGjP32x512 = 6,
+                 kGjP32x512 = 6, kLu64 = 7,
                  // FP32 working matrices (mixed forms): panel width x threads (x rows per thread)
                  kGjF64x512 = 11, kGjF32x512 = 12, kGjF32x256 = 13, kGjF32x512r2 = 14, kGjF48x512r2 = 15,
-                 kGjPF32x512 = 16 };
+                 kGjPF32x512 = 16, kLu32 = 17 };
 bool gj_variant_ok(int variant, int mmax);
 bool gj_variant_f32(int variant);
 // workgroups of the batched inversion for npatch blocks (the fewest rounds
@@ -78,6 +81,46 @@ void launch_gj_batched_f32(float *blocks, const int64_t *boff, const int *pm, co
                            int *perm, int *used, int npatch, int mmax, int *status, int grid,
                            const int *sched, hipStream_t st, int variant = kGjAuto,
                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// the operator's values with every row scaled by a power of two to a largest
+// entry in [1/2, 1) (rounded to T), and the rows' exponents
+template <typename T>
+void launch_scale_rows(const CsrView<double> &J, T *out, int *er, hipStream_t st);
+// LU inversion of the blocks: launch_lu_blocks factors the blocks order[0 ..
+// nblk) in place (rows never exchanged, perm at poff[k] the pivot rows;
+// status[k] as above), launch_lu_rows then writes rows of the inverses from
+// the factors, in the layout of launch_pack_owned, for up to kLuRowsItems
+// task lists (levels) a launch.  ev0/ev1: events at the first kernel's start
+// and the last one's end.
+template <typename T>
+struct LuRowsItem {
+  const T *blocks;                            // the level's factored blocks
+  const int64_t *boff, *pdof_off, *woff;
+  const int *pm, *po, *row_off, *row_local;   // rows wanted of each block (ascending local indices)
+  const int *task_patch, *task_row0, *perm;
+  const int *dof, *er;                        // the blocks' dofs (at pdof_off); the rows' exponents, or NULL (unscaled)
+  T *W;
+  float *cscale;                              // NULL, or the columns' largest magnitudes (zeroed beforehand)
+};
+constexpr int kLuRowsItems = 8;
+template <typename T>
+struct LuRowsBatch {
+  int count;
+  int task0[kLuRowsItems + 1];
+  LuRowsItem<T> it[kLuRowsItems];
+};
+template <typename T>
+void launch_lu_blocks(T *blocks, const int64_t *boff, const int *pm, const int64_t *poff, int *perm, int *status,
+                      const int *order, int nblk, int mmax, hipStream_t st, hipEvent_t ev0 = nullptr);
+template <typename T>
+void launch_lu_rows(const LuRowsItem<T> *items, const int *ntasks, int count, int mmax, hipStream_t st,
+                    hipEvent_t ev1 = nullptr);
+// the 16-bit copy of a task list's FP32 rows (grouped layout, or the rows' own
+// one without woff16), from the columns' scales; writes the rows' scales
+void launch_pack16_rows(const float *rows, const int *pm, const int *po, const int *row_off, const int64_t *pdof_off,
+                        const int64_t *woff, const int64_t *woff16, const int *task_patch, const int *task_row0,
+                        int ntask, const float *cscale, uint16_t *W16, int w16_kind, float *wscale, hipStream_t st);
+// columns without a nonzero entry get scale 1
+void launch_scale_fix(float *cscale, int64_t n, hipStream_t st);
 // The coarsest operator's dofs split into D, whose row and column hold only
 // the diagonal entry (Dirichlet rows of a symmetrically eliminated
 // operator), and the free rest F: the operator is diag(a_D) + A_FF up to
@@ -110,7 +153,7 @@ struct BandView {
   int *perm = nullptr, *plo = nullptr, *scale = nullptr;
 };
 constexpr int kEquilSteps = 4;
-constexpr int kLuBandSlots = 320;    // waiting rows that one wave holds without spilling (5 a lane)
+constexpr int kLuBandSlots = 384;    // waiting rows at most (six a lane of the factoring wave)
 constexpr int kLuBandMax = 2560;     // largest ordered block (20 panels a wave in k_lu_band_rows)
 // once before the first lu_coarse (which may be captured into a graph)
 void lu_coarse_prepare();
@@ -139,14 +182,14 @@ void launch_pack_owned(const TB *blocks, const int64_t *boff, const int *pm, con
                        const int *task_patch, const int *task_row0, int ntask, double *W64,
                        float *W32, uint16_t *W16, int w16_kind, float *wscale,
                        const int64_t *pdof_off, const float *cscale, const int *perm,
-                       const int64_t *woff16, hipStream_t st);
+                       const int64_t *woff16, const int *dof, const int *er, hipStream_t st);
 // 16-bit storage: per-column scales of the owned rows of every block inverse
 template <typename TB>
 void launch_colscale(const TB *blocks, const int64_t *boff, const int *pm, const int *po,
                      const int *own_off, const int *own_local, const int64_t *pdof_off,
                      const int *task_patch, const int *task_row0, int ntask, int64_t total_cols,
-                     float *cscale, const int *perm, int mmax, hipStream_t st, bool first = true,
-                     bool last = true);
+                     float *cscale, const int *perm, const int *dof, const int *er, int mmax, hipStream_t st,
+                     bool first = true, bool last = true);
 
 // ---- smoother (a5): e[out] += omega * W_k s[I_k] for every owned row
 //      (16-bit: W_k = diag(rs) W16 diag(cs), two-sided scaling)

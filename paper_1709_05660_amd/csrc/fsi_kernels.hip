@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void k_extract_map(int nrows_total, const int 
   const int m = pm[k];
   const int *d = dof + pdof_off[k];
   const int g = d[i];
-  const int64_t base = boff[k] + (int64_t)i * m;
+  const int64_t base = boff[k] + (int64_t)i * block_ld(m);
   const int64_t s0 = slot_off[t];
   for (int p = rowptr[g] + lane; p < rowptr[g + 1]; p += 64) {
     const int c = col[p];
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(256) void k_extract_map(int nrows_total, const int 
         hi = mid - 1;
     }
     src[s0 + (p - rowptr[g])] = p;
-    dst[s0 + (p - rowptr[g])] = at < 0 ? -1 : (int)(base + at);
+    dst[s0 + (p - rowptr[g])] = at < 0 ? -1 : (int)(unsigned)(base + at);
   }
 }
 
@@ -308,27 +308,25 @@ void launch_extract_map(const CsrView<double> &J, const int *pm, const int64_t *
 
 // B_k = J[I_k, I_k]: one thread per slot of the map (FP32 blocks: the values
 // rounded to single precision, the working matrices of the mixed forms)
-template <typename TB>
+template <typename TV, typename TB>
 __global__ __launch_bounds__(256) void k_extract(int64_t nslots, const int *__restrict__ src,
                                                  const int *__restrict__ dst,
-                                                 const double *__restrict__ val,
+                                                 const TV *__restrict__ val,
                                                  TB *__restrict__ blocks) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= nslots) return;
   const int q = dst[e];
-  if (q >= 0) blocks[q] = (TB)val[src[e]];
+  if (q != -1) blocks[(unsigned)q] = (TB)val[src[e]];
 }
 
-void launch_extract(const double *val, int64_t nslots, const int *src, const int *dst,
-                    double *blocks, hipStream_t st) {
+template <typename TV, typename TB>
+void launch_extract(const TV *val, int64_t nslots, const int *src, const int *dst, TB *blocks, hipStream_t st) {
   if (nslots == 0) return;
   k_extract<<<(unsigned)((nslots + 255) / 256), 256, 0, st>>>(nslots, src, dst, val, blocks);
 }
-void launch_extract(const double *val, int64_t nslots, const int *src, const int *dst,
-                    float *blocks, hipStream_t st) {
-  if (nslots == 0) return;
-  k_extract<<<(unsigned)((nslots + 255) / 256), 256, 0, st>>>(nslots, src, dst, val, blocks);
-}
+template void launch_extract<double, double>(const double *, int64_t, const int *, const int *, double *, hipStream_t);
+template void launch_extract<double, float>(const double *, int64_t, const int *, const int *, float *, hipStream_t);
+template void launch_extract<float, float>(const float *, int64_t, const int *, const int *, float *, hipStream_t);
 
 // ------------------------------------------------------------------ packing of owned rows
 __device__ inline uint16_t to_bf16(float f) {
@@ -347,6 +345,8 @@ __device__ inline float from_fp16(uint16_t u) {
   return __half2float(h);
 }
 
+// With er, the blocks were inverted with their rows scaled by 2^er (of the
+// row's dof; see launch_scale_rows), which the inverse's columns take here.
 // The Gauss-Jordan result S holds every block inverse up to its pivot
 // permutations: Binv[i][c] = S[perm[i]][used[c]], equivalently physical
 // column p of S is logical column perm[p] (per-patch arrays at pdof_off[k]).
@@ -366,7 +366,8 @@ __global__ __launch_bounds__(256) void k_colscale(const TB *__restrict__ blocks,
                                                   const int64_t *__restrict__ pdof_off,
                                                   const int *__restrict__ task_patch,
                                                   const int *__restrict__ task_row0, float *cscale,
-                                                  const int *__restrict__ perm) {
+                                                  const int *__restrict__ perm, const int *__restrict__ dof,
+                                                  const int *__restrict__ er) {
   extern __shared__ unsigned cmax[];   // the largest block's columns (sized at launch)
   const int k = task_patch[blockIdx.x], r0 = task_row0[blockIdx.x];
   const int m = pm[k], nr = min(64, po[k] - r0);
@@ -375,29 +376,35 @@ __global__ __launch_bounds__(256) void k_colscale(const TB *__restrict__ blocks,
   for (int c = threadIdx.x; c < m; c += blockDim.x) cmax[c] = 0u;
   __syncthreads();
   for (int r = 0; r < nr; ++r) {
-    const TB *row = B + (int64_t)pk[own_local[own_off[k] + r0 + r]] * m;
+    const TB *row = B + (int64_t)pk[own_local[own_off[k] + r0 + r]] * block_ld(m);
     for (int p = threadIdx.x; p < m; p += blockDim.x)
       atomicMax(&cmax[pk[p]], __float_as_uint((float)fabs((double)row[p])));
   }
   __syncthreads();
+  // (a power of two: the maximum of the scaled entries)
   for (int c = threadIdx.x; c < m; c += blockDim.x)
-    atomicMax(reinterpret_cast<unsigned *>(cscale + pdof_off[k]) + c, cmax[c]);
+    atomicMax(reinterpret_cast<unsigned *>(cscale + pdof_off[k]) + c,
+              er ? __float_as_uint(ldexpf(__uint_as_float(cmax[c]), er[dof[pdof_off[k] + c]])) : cmax[c]);
 }
 // columns with no nonzero owned entry get scale 1
 __global__ void k_scale_fix(float *cs, int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n && !(cs[i] > 0.0f)) cs[i] = 1.0f;
 }
+void launch_scale_fix(float *cscale, int64_t n, hipStream_t st) {
+  k_scale_fix<<<cdiv(n, 256), 256, 0, st>>>(cscale, n);
+}
 template <typename TB>
 void launch_colscale(const TB *blocks, const int64_t *boff, const int *pm, const int *po,
                      const int *own_off, const int *own_local, const int64_t *pdof_off,
                      const int *task_patch, const int *task_row0, int ntask, int64_t total_cols,
-                     float *cscale, const int *perm, int mmax, hipStream_t st, bool first, bool last) {
+                     float *cscale, const int *perm, const int *dof, const int *er, int mmax, hipStream_t st,
+                     bool first, bool last) {
   if (first) launch_fill_f32(cscale, total_cols, 0.0f, st);
   if (ntask)
     k_colscale<<<ntask, 256, sizeof(unsigned) * mmax, st>>>(blocks, boff, pm, po, own_off, own_local, pdof_off,
-                                                            task_patch, task_row0, cscale, perm);
-  if (last) k_scale_fix<<<cdiv(total_cols, 256), 256, 0, st>>>(cscale, total_cols);
+                                                            task_patch, task_row0, cscale, perm, dof, er);
+  if (last) launch_scale_fix(cscale, total_cols, st);
 }
 
 // Owned rows of Binv_k in task-contiguous column-major order: the rows of
@@ -424,7 +431,8 @@ __global__ __launch_bounds__(256) void k_pack_owned(const TB *__restrict__ block
                                                     float *wscale, const int64_t *__restrict__ pdof_off,
                                                     const float *__restrict__ cscale,
                                                     const int *__restrict__ perm,
-                                                    const int64_t *__restrict__ woff16) {
+                                                    const int64_t *__restrict__ woff16,
+                                                    const int *__restrict__ dof, const int *__restrict__ er) {
   __shared__ double tile[64][65];
   __shared__ int64_t rowoff[64];
   __shared__ double rsc[64];
@@ -433,15 +441,19 @@ __global__ __launch_bounds__(256) void k_pack_owned(const TB *__restrict__ block
   const int *pk = perm + pdof_off[k];
   const TB *B = blocks + boff[k];
   const float *cs = W16 ? cscale + pdof_off[k] : nullptr;
+  const int *dk = dof + pdof_off[k];
   const int tid = threadIdx.x;
-  if (tid < 64) rowoff[tid] = tid < nr ? (int64_t)pk[own_local[own_off[k] + r0 + tid]] * m : 0;
+  if (tid < 64) rowoff[tid] = tid < nr ? (int64_t)pk[own_local[own_off[k] + r0 + tid]] * block_ld(m) : 0;
   __syncthreads();
   if (W16) {
     const int r = tid >> 2, sub = tid & 3;   // 4 threads per row
     double mx = 0.0;
     if (r < nr) {
 #pragma unroll 8
-      for (int p = sub; p < m; p += 4) mx = fmax(mx, fabs((double)B[rowoff[r] + p]) / (double)cs[pk[p]]);
+      for (int p = sub; p < m; p += 4) {
+        const double a = fabs((double)B[rowoff[r] + p]);
+        mx = fmax(mx, (er ? ldexp(a, er[dk[pk[p]]]) : a) / (double)cs[pk[p]]);
+      }
     }
     mx = fmax(mx, __shfl_xor(mx, 1, 4));
     mx = fmax(mx, __shfl_xor(mx, 2, 4));
@@ -474,7 +486,7 @@ __global__ __launch_bounds__(256) void k_pack_owned(const TB *__restrict__ block
       const int p = idx >> 6, r = idx & 63;
       if (r < nr && q0 + p < m) {
         const int c = pk[q0 + p];
-        const double v = tile[r][p];
+        const double v = er ? ldexp(tile[r][p], er[dk[c]]) : tile[r][p];
         const int64_t dst = wk + (int64_t)c * nr + r;
         if (W64) W64[dst] = v;
         if (W32) W32[dst] = (float)v;
@@ -494,21 +506,21 @@ void launch_pack_owned(const TB *blocks, const int64_t *boff, const int *pm, con
                        const int *task_patch, const int *task_row0, int ntask, double *W64,
                        float *W32, uint16_t *W16, int w16_kind, float *wscale,
                        const int64_t *pdof_off, const float *cscale, const int *perm,
-                       const int64_t *woff16, hipStream_t st) {
+                       const int64_t *woff16, const int *dof, const int *er, hipStream_t st) {
   if (ntask == 0) return;
   k_pack_owned<<<ntask, 256, 0, st>>>(blocks, boff, pm, po, woff, own_off, own_local, task_patch,
                                       task_row0, W64, W32, W16, w16_kind, wscale, pdof_off, cscale,
-                                      perm, woff16);
+                                      perm, woff16, dof, er);
 }
 #define FSI_PACK_INST(TB)                                                                            \
   template void launch_colscale<TB>(const TB *, const int64_t *, const int *, const int *, const int *, \
                                     const int *, const int64_t *, const int *, const int *, int,       \
-                                    int64_t, float *, const int *, int, hipStream_t, bool, bool);      \
+                                    int64_t, float *, const int *, const int *, const int *, int, hipStream_t, bool, bool); \
   template void launch_pack_owned<TB>(const TB *, const int64_t *, const int *, const int *,           \
                                       const int64_t *, const int *, const int *, const int *,          \
                                       const int *, int, double *, float *, uint16_t *, int, float *,   \
                                       const int64_t *, const float *, const int *, const int64_t *,    \
-                                      hipStream_t);
+                                      const int *, const int *, hipStream_t);
 FSI_PACK_INST(double)
 FSI_PACK_INST(float)
 #undef FSI_PACK_INST
@@ -949,12 +961,12 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_ilu_factor(IluView v, T *__restrict__ blocks, int *__restrict__ status,
                                                     int status_base) {
   const int b = blockIdx.x, tid = threadIdx.x;
-  const int k = v.patch[b], m = v.pm[k], r0 = v.row0[b];
+  const int k = v.patch[b], m = v.pm[k], ld = block_ld(m), r0 = v.row0[b];
   T *A = blocks + v.boff[k];
   const uint32_t *mk = v.mask + v.moff[b];
   int fail = 0;
   for (int kk = 0; kk < m; ++kk) {
-    const T akk = A[(int64_t)kk * m + kk];
+    const T akk = A[(int64_t)kk * ld + kk];
     if (!(akk != (T)0) || !isfinite((double)akk)) {
       fail = kk + 1;
       break;
@@ -965,14 +977,14 @@ __global__ __launch_bounds__(256) void k_ilu_factor(IluView v, T *__restrict__ b
       const int i = v.crow[ca + t / nu], j = v.ucol[ua + t % nu];
       const int64_t bit = (int64_t)i * m + j;
       if ((mk[bit >> 5] >> (bit & 31)) & 1u) {
-        const T l = A[(int64_t)i * m + kk] / akk;
-        A[(int64_t)i * m + j] -= l * A[(int64_t)kk * m + j];
+        const T l = A[(int64_t)i * ld + kk] / akk;
+        A[(int64_t)i * ld + j] -= l * A[(int64_t)kk * ld + j];
       }
     }
     __threadfence_block();
     __syncthreads();
     for (int t = tid; t < nl; t += 256) {
-      const int64_t q = (int64_t)v.crow[ca + t] * m + kk;
+      const int64_t q = (int64_t)v.crow[ca + t] * ld + kk;
       A[q] = A[q] / akk;
     }
     __threadfence_block();
@@ -991,7 +1003,7 @@ template <typename T, typename V>
 __global__ void k_ilu_gather(const T *__restrict__ blocks, const int *__restrict__ pos, int64_t n,
                              V *__restrict__ out) {
   const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q < n) out[q] = (V)blocks[pos[q]];
+  if (q < n) out[q] = (V)blocks[(unsigned)pos[q]];
 }
 template <typename T, typename V>
 void launch_ilu_gather(const T *blocks, const int *pos, int64_t n, V *out, hipStream_t st) {

@@ -17,9 +17,13 @@
 // the rows still waiting, which are updated by
 //     A[i][j] += sum_t PC[i][t] A[perm[16 p + t]][j]
 // for the columns j beyond the panel; a pivot row keeps its values there.
+#include <hip/hip_bf16.h>
+#include <hip/hip_ext.h>
+#include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <climits>
 #include <mutex>
 
@@ -43,128 +47,205 @@ struct alignas(16) Quad {
 };
 
 // the pivot row (lane ll, register row ql) into scalars
-template <typename T, int R, int Q = 0>
-__device__ __forceinline__ void lu_take(const T (&v)[R][kLuNb], int ql, int ll, T (&prow)[kLuNb]) {
+template <typename T, int R, int NC, int Q = 0>
+__device__ __forceinline__ void lu_take(const T (&v)[R][NC], int ql, int ll, T (&prow)[NC]) {
   if (Q == R - 1 || ql == Q) {
 #pragma unroll
-    for (int c = 0; c < kLuNb; ++c) prow[c] = readlane(v[Q][c], ll);
+    for (int c = 0; c < NC; ++c) prow[c] = readlane(v[Q][c], ll);
   } else if constexpr (Q + 1 < R) {
-    lu_take<T, R, Q + 1>(v, ql, ll, prow);
+    lu_take<T, R, NC, Q + 1>(v, ql, ll, prow);
   }
 }
 
-// One panel of 16 columns factored by one wave.  Lane l holds the rows of
-// slots l + 64 q in v[q]; step[q] is -1 for a row that waits for its pivot (a
-// candidate), and becomes the step at which it is the pivot; other slots hold
-// zeros and a step >= 16.  Every row is eliminated in every column of the panel
-// (Gauss-Jordan inside the panel), so that the rows end as described above; a
-// pivot row stays unscaled until the end (1 in its own column, and it takes
-// the later eliminations like any other), so that a step has no branch that
-// moves rows between registers.  Returns 0, or 1 + the first step (0-based, in
-// the panel) whose pivot is zero or not finite (the steps go on without a
-// branch; the result is unusable).
-template <typename T, int R>
-__device__ __forceinline__ int lu_panel(T (&v)[R][kLuNb], int (&step)[R]) {
+// the pivot steps on columns t, t + 1, ... of a group of NC (see lu_columns);
+// t0: the group's first step in the panel
+template <typename T, int R, int NC, int t>
+__device__ __forceinline__ void lu_steps(T (&v)[R][NC], int (&step)[R], int t0, T *scale, int &fail) {
   const int lane = threadIdx.x & 63;
-  int fail = 0;
-  T scale[R];
+  double key = -1.0;
+  T sv = 1;
 #pragma unroll
-  for (int q = 0; q < R; ++q) scale[q] = 1;
-#pragma unroll
-  for (int t = 0; t < kLuNb; ++t) {
-    double key = -1.0;
-    T sv = 1;
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const double kq = pivot_key((double)v[q][t], q * 64 + lane);
-      if (step[q] < 0 && kq > key) {
-        key = kq;
-        sv = v[q][t];
-      }
-    }
-    const T dl = recip(sv);   // every lane inverts its own candidate during the reduction
-    const double best = wave_max<true>(key);
-    const double bv = key_value(best);
-    const bool bad = !(best >= 0.0) || !(bv > 0.0) || bv >= key_value(pivot_key(DBL_MAX, 0));
-    fail = fail == 0 && bad ? t + 1 : fail;
-    const int slot = __builtin_amdgcn_readfirstlane(key_row(best));
-    const int ll = slot & 63;
-    const T d = readlane(dl, ll);
-    T prow[kLuNb];
-    lu_take<T, R>(v, slot >> 6, ll, prow);
-#pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const bool own = slot == q * 64 + lane;
-      const T fd = own ? (T)0 : v[q][t] * d;
-      scale[q] = own ? d : scale[q];
-      step[q] = own ? t : step[q];
-#pragma unroll
-      for (int c = 0; c < kLuNb; ++c) v[q][c] = c == t ? (own ? (T)1 : -fd) : v[q][c] - fd * prow[c];
+  for (int q = 0; q < R; ++q) {
+    const double kq = pivot_key((double)v[q][t], q * 64 + lane);
+    if (step[q] < 0 && kq > key) {
+      key = kq;
+      sv = v[q][t];
     }
   }
+  const T dl = recip(sv);   // every lane inverts its own candidate during the reduction
+  const double best = wave_max<true>(key);
+  const double bv = key_value(best);
+  const bool bad = !(best >= 0.0) || !(bv > 0.0) || bv >= key_value(pivot_key(DBL_MAX, 0));
+  fail = fail == 0 && bad ? t0 + t + 1 : fail;
+  const int slot = __builtin_amdgcn_readfirstlane(key_row(best));
+  const int ll = slot & 63;
+  const T d = readlane(dl, ll);
+  if (lane == 0) scale[t] = d;
+  T prow[NC];
+  lu_take<T, R, NC>(v, slot >> 6, ll, prow);
 #pragma unroll
-  for (int q = 0; q < R; ++q)
+  for (int q = 0; q < R; ++q) {
+    const bool own = slot == q * 64 + lane;
+    const T fd = own ? (T)0 : v[q][t] * d;
+    step[q] = own ? t0 + t : step[q];
 #pragma unroll
-    for (int c = 0; c < kLuNb; ++c) v[q][c] *= scale[q];
+    for (int c = 0; c < NC; ++c) {
+      v[q][c] = c == t ? (own ? (T)1 : -fd) : v[q][c] - fd * prow[c];
+      // keeps each step's work in the step: deferred, the columns that no
+      // later step searches would hold every pivot row in scalars to the end
+      asm volatile("" : "+v"(v[q][c]));
+    }
+  }
+  if constexpr (t + 1 < NC) lu_steps<T, R, NC, t + 1>(v, step, t0, scale, fail);
+}
+
+// Shared memory of a factorization: by the parity of a panel its rows (first
+// the panel being factored, then its factors for the updates), the matrix row
+// in each slot or -1, the panel's pivot rows in step order and the slots in
+// use or the failure; (banded) the panel at which each slot's row entered; the
+// factoring wave's reciprocals and pivot slots.  PB: panel buffers (one where
+// the updates read the factors from the matrix).
+template <typename T, int PB>
+struct LuLds {
+  T *base;
+  int nslot;
+  __device__ __forceinline__ T *panel(int p) const { return base + (p & (PB - 1)) * nslot * kLuStride<T>; }
+  __device__ __forceinline__ T *scale() const { return base + PB * nslot * kLuStride<T>; }
+  __device__ __forceinline__ int *ints() const { return reinterpret_cast<int *>(scale() + kLuNb); }
+  __device__ __forceinline__ int *row(int p) const { return ints() + (p & 1) * nslot; }
+  __device__ __forceinline__ int *entry() const { return ints() + 2 * nslot; }
+  __device__ __forceinline__ int *piv(int p) const { return ints() + 3 * nslot + (p & 1) * kLuNb; }
+  __device__ __forceinline__ int *slots() const { return ints() + 3 * nslot + 2 * kLuNb; }
+  __device__ __forceinline__ int *result(int p) const { return ints() + 3 * nslot + 3 * kLuNb + (p & 1); }
+};
+template <typename T>
+static inline size_t lu_lds_bytes(int nslot, int pb) {
+  return sizeof(T) * ((size_t)pb * nslot * kLuStride<T> + kLuNb) + sizeof(int) * (3 * (size_t)nslot + 3 * kLuNb + 2);
+}
+
+// (No variant may spill: once the compiler put the spills of a lane's slot
+// rows into one side of a divergent branch, and the lanes of the other side
+// later stored to rows read from stale scratch memory.)
+// Columns [c0, c0 + NC) of the panel at P factored by one wave.  Lane l holds
+// the rows of slots l + 64 q in registers; step[q] is -1 for a row that waits
+// for its pivot (a candidate) and becomes the step at which it is the pivot,
+// other slots have a step >= 16 and take no part.  Every row is eliminated in every
+// column of the group (Gauss-Jordan inside it); a pivot row stays unscaled
+// until the end (1 in its own column, and it takes the later eliminations like
+// any other), so that a step has no branch that moves rows between registers.
+// Returns 0, or 1 + the first step whose pivot is zero or not finite (the
+// steps go on without a branch; the result is unusable).
+template <typename T, int R, int NC, int PB>
+__device__ __forceinline__ int lu_columns(T *P, int c0, int (&step)[R], const LuLds<T, PB> &L) {
+  constexpr int LS = kLuStride<T>;
+  const int lane = threadIdx.x & 63;
+  T v[R][NC];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const bool use = step[q] < kLuNb;
+    const T *x = P + (use ? q * 64 + lane : 0) * LS + c0;
+#pragma unroll
+    for (int g = 0; g < NC / 4; ++g) {
+      const Quad<T> y = *reinterpret_cast<const Quad<T> *>(x + 4 * g);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[q][4 * g + k] = use ? y.v[k] : (T)0;
+    }
+  }
+  int fail = 0;
+  lu_steps<T, R, NC, 0>(v, step, c0, L.scale(), fail);
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const bool pivot = step[q] >= c0 && step[q] < c0 + NC;
+    const T sc = pivot ? L.scale()[step[q] - c0] : (T)1;
+    if (pivot) L.slots()[step[q]] = q * 64 + lane;
+    if (step[q] < kLuNb) {
+      T *x = P + (q * 64 + lane) * LS + c0;
+#pragma unroll
+      for (int g = 0; g < NC / 4; ++g) {
+        Quad<T> y;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y.v[k] = v[q][4 * g + k] * sc;
+        *reinterpret_cast<Quad<T> *>(x + 4 * g) = y;
+      }
+    }
+  }
   return fail;
 }
 
-// Shared memory of a factorization, by the parity of a panel: its rows (first
-// the panel being factored, then its factors for the updates), the matrix row
-// in each slot or -1, the panel's pivot rows in step order, the slots in use
-// or the failure; and (banded) the panel at which each slot's row entered.
-template <typename T>
-struct LuLds {
-  T *base;
-  int *ints;
-  int nslot;
-  __device__ __forceinline__ T *panel(int p) const { return base + (p & 1) * nslot * kLuStride<T>; }
-  __device__ __forceinline__ int *row(int p) const { return ints + (p & 1) * nslot; }
-  __device__ __forceinline__ int *entry() const { return ints + 2 * nslot; }
-  __device__ __forceinline__ int *piv(int p) const { return ints + 3 * nslot + (p & 1) * kLuNb; }
-  __device__ __forceinline__ int *result(int p) const { return ints + 3 * nslot + 2 * kLuNb + (p & 1); }
-};
-static inline size_t lu_lds_bytes(int nslot, size_t elem, int stride) {
-  return 2 * (size_t)nslot * stride * elem + sizeof(int) * (3 * (size_t)nslot + 2 * kLuNb + 4);
+// A factored group of NC columns applied to the panel's other columns (one
+// wave, on the matrix cores, in LDS): row i takes sum_t PC[i][t] X[t], X the
+// group's pivot rows before the update, which start from zero.
+template <typename T, int NC, int PB>
+__device__ __forceinline__ void lu_cross(T *P, int c0, int nrt, const LuLds<T, PB> &L) {
+  typedef Mfma16<T> MM;
+  typedef typename MM::acc acc;
+  constexpr int LS = kLuStride<T>, KK = NC / 4;
+  const int lane = threadIdx.x & 63, jl = lane & 15, kq = lane >> 4;
+  const bool other = jl < c0 || jl >= c0 + NC;
+  const int *slots = L.slots() + c0;
+  T bx[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    const T x = P[slots[KK * kq + kk] * LS + jl];
+    bx[kk] = other ? x : (T)0;
+  }
+#pragma unroll
+  for (int t = 0; t < NC; t += 4)
+    if (other) P[slots[t + kq] * LS + jl] = 0;
+  for (int rt = 0; rt < nrt; ++rt) {
+    const T *a = P + (rt * 16 + jl) * LS + c0 + KK * kq;
+    acc c;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c[r] = P[(rt * 16 + MM::row(r, kq)) * LS + jl];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) c = MM::mma(a[kk], bx[kk], c);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) P[(rt * 16 + MM::row(r, kq)) * LS + jl] = c[r];
+  }
 }
 
-// The factoring wave's part of panel p: the rows of slots [0, cnt) from LDS
-// (with the panel's columns up to date), their factors to LDS and to the
-// matrix, and the slots of the next panel.  Banded: a row keeps its slot
+// The factoring wave's part of panel p: the rows of slots [0, cnt) in LDS
+// (with the panel's columns up to date) factored in groups of NC columns (as
+// many as its registers hold with R rows a lane), the factors to the matrix
+// and to LDS, and the slots of the next panel.  Banded: a row keeps its slot
 // until it is a pivot, freed slots go to the rows [hi, hinext) that enter
 // next.  Dense: the rows left are moved together.  Returns the slots in use
 // for the next panel, or -1 - step on a failing pivot.
-template <typename T, int R, bool BAND>
-__device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, int w, int cnt, int hi,
-                                         int hinext, const LuLds<T> &L, int *__restrict__ perm,
-                                         int *__restrict__ plo) {
+template <typename T, int R, int NC, bool BAND, int PB>
+__device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, int w, int cnt, int hi, int hinext,
+                                         const LuLds<T, PB> &L, int *__restrict__ perm, int *__restrict__ plo) {
   constexpr int LS = kLuStride<T>;
   const int lane = threadIdx.x & 63, p0 = p * kLuNb;
   const unsigned long long below = (1ull << lane) - 1;
   T *P = L.panel(p);
   const int *row = L.row(p);
   int *rown = L.row(p + 1);
-  T v[R][kLuNb];
-  int ri[R], step[R];
+  int step[R];
   int unit = kLuNb - w;   // a last panel of w < 16 columns: the other pivots are unit rows in free slots
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const int s = q * 64 + lane;
-    ri[q] = s < cnt ? row[s] : -1;
-    const unsigned long long fr = __ballot(ri[q] < 0);
+    const bool taken = s < cnt && row[s] >= 0, open = !taken && s < L.nslot;
+    const unsigned long long fr = __ballot(open);
     const int k = __popcll(fr & below);
-    const int one = ri[q] < 0 && k < unit ? kLuNb - unit + k : -1;
+    const bool one = open && k < unit;
+    if (one)
+#pragma unroll
+      for (int c = 0; c < kLuNb; ++c) P[s * LS + c] = c == kLuNb - unit + k ? (T)1 : (T)0;
     unit -= min(unit, (int)__popcll(fr));
-    step[q] = ri[q] >= 0 || one >= 0 ? -1 : kLuNb;
-#pragma unroll
-    for (int g = 0; g < kLuNb / 4; ++g) {
-      const Quad<T> x = *reinterpret_cast<const Quad<T> *>(P + max(min(s, cnt - 1), 0) * LS + 4 * g);
-#pragma unroll
-      for (int k2 = 0; k2 < 4; ++k2)
-        v[q][4 * g + k2] = ri[q] >= 0 ? x.v[k2] : 4 * g + k2 == one ? (T)1 : (T)0;
+    step[q] = taken || one ? -1 : kLuNb;
+  }
+  if (lane < kLuNb) L.slots()[lane] = 0;
+  int f = 0;
+  if constexpr (NC == kLuNb) {
+    f = lu_columns<T, R, NC, PB>(P, 0, step, L);
+  } else {
+    for (int c0 = 0; c0 < kLuNb; c0 += NC) {
+      const int g = lu_columns<T, R, NC, PB>(P, c0, step, L);
+      f = f ? f : g;
+      lu_cross<T, NC, PB>(P, c0, (cnt + 15) >> 4, L);
     }
   }
-  const int f = lu_panel<T, R>(v, step);
   if (f) return -1 - (p0 + f - 1);
   int pl = p;   // the first panel whose columns a pivot row of this panel has factors in
   int base = 0, need = hinext - hi, next = hi;   // dense: rows kept so far; banded: rows still to place
@@ -172,23 +253,22 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const int s = q * 64 + lane;
-    const bool pivot = ri[q] >= 0 && step[q] >= 0, kept = ri[q] >= 0 && !pivot;
-    if (ri[q] >= 0) {
-      T *row16 = A + ri[q] * ld + p0;
+    const int ri = s < cnt ? row[s] : -1;
+    const bool pivot = ri >= 0 && step[q] >= 0, kept = ri >= 0 && !pivot;
+    Quad<T> x[kLuNb / 4];
 #pragma unroll
-      for (int g = 0; g < kLuNb / 4; ++g) {
-        Quad<T> x;
+    for (int g = 0; g < kLuNb / 4; ++g) {
+      const Quad<T> y = *reinterpret_cast<const Quad<T> *>(P + (ri >= 0 ? s : 0) * LS + 4 * g);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x.v[k] = v[q][4 * g + k];
-        *reinterpret_cast<Quad<T> *>(row16 + 4 * g) = x;
-      }
+      for (int k = 0; k < 4; ++k) x[g].v[k] = y.v[k];
+      if (ri >= 0) *reinterpret_cast<Quad<T> *>(A + ri * ld + p0 + 4 * g) = x[g];
     }
-    if (pivot && step[q] < w) {   // (a failing panel may give a row a step past the last)
-      perm[p0 + step[q]] = ri[q];
-      L.piv(p)[step[q]] = ri[q];
+    if (pivot && step[q] < w) {
+      perm[p0 + step[q]] = ri;
+      L.piv(p)[step[q]] = ri;
       if (BAND) pl = min(pl, L.entry()[s]);
     }
-    int slot, occupant = kept ? ri[q] : -1;
+    int slot, occupant = kept ? ri : -1;
     bool store;
     if constexpr (BAND) {
       // a free slot takes the next entering row, in slot order
@@ -207,6 +287,7 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
       const unsigned long long occ = __ballot(occupant >= 0);
       if (occ) last = q * 64 + 64 - __clzll(occ);
     } else {
+      // (slots below the ones read so far)
       const unsigned long long kb = __ballot(kept);
       slot = base + __popcll(kb & below);
       base += __popcll(kb);
@@ -215,12 +296,13 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
     }
     if (store) {
       rown[slot] = occupant;
+      if constexpr (PB == 2) {
 #pragma unroll
-      for (int g = 0; g < kLuNb / 4; ++g) {
-        Quad<T> x;
+        for (int g = 0; g < kLuNb / 4; ++g) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) x.v[k] = kept ? v[q][4 * g + k] : (T)0;
-        *reinterpret_cast<Quad<T> *>(P + slot * LS + 4 * g) = x;
+          for (int k = 0; k < 4; ++k) x[g].v[k] = kept ? x[g].v[k] : (T)0;
+          *reinterpret_cast<Quad<T> *>(P + slot * LS + 4 * g) = x[g];
+        }
       }
     }
   }
@@ -234,8 +316,10 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
     const int s = base + lane;
     if (lane < 16 && s < ((base + 15) & ~15)) {
       rown[s] = -1;
+      if constexpr (PB == 2) {
 #pragma unroll
-      for (int k = 0; k < kLuNb; ++k) P[s * LS + k] = 0;
+        for (int k = 0; k < kLuNb; ++k) P[s * LS + k] = 0;
+      }
     }
   }
   return last;
@@ -246,8 +330,8 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
 // first column; before panel p the rows [0, hi[p]) may be nonzero in its
 // columns, and their last column is below cend[p]; at most nslot rows wait at
 // a time.  nslot: slots in LDS, a multiple of 16.
-template <typename T, int RMAX, bool BAND>
-__device__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__restrict__ hi,
+template <typename T, int RMAX, bool BAND, int PB>
+__device__ __forceinline__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__restrict__ hi,
                           const int *__restrict__ cend, int nslot, int *__restrict__ perm, int *__restrict__ plo,
                           int *__restrict__ status, unsigned char *lds) {
   typedef Mfma16<T> MM;
@@ -256,9 +340,8 @@ __device__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__res
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int jl = lane & 15, kq = lane >> 4;
-  LuLds<T> L;
+  LuLds<T, PB> L;
   L.base = reinterpret_cast<T *>(lds);
-  L.ints = reinterpret_cast<int *>(L.base + 2 * nslot * LS);
   L.nslot = nslot;
   const int np = (n + kLuNb - 1) / kLuNb;
   int cnt = BAND ? hi[0] : n;
@@ -288,8 +371,15 @@ __device__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__res
       for (int r = 0; r < 4; ++r) c[r] = A[max(row[rt * 16 + MM::row(r, kq)], 0) * ld + c0 + jl];
       return c;
     };
-    auto update = [&](int rt, const T (&bx)[4], acc c) {
-      const Quad<T> a = *reinterpret_cast<const Quad<T> *>(F + (rt * 16 + jl) * LS + 4 * kq);
+    // the previous panel's factors of a tile's rows, from LDS or the matrix
+    // (there the slots without a row repeat row 0; their results go nowhere)
+    auto load_f = [&](int rt) {
+      if constexpr (PB == 2)
+        return *reinterpret_cast<const Quad<T> *>(F + (rt * 16 + jl) * LS + 4 * kq);
+      else
+        return *reinterpret_cast<const Quad<T> *>(A + max(row[rt * 16 + jl], 0) * ld + p0 - kLuNb + 4 * kq);
+    };
+    auto update = [&](const Quad<T> &a, const T (&bx)[4], acc c) {
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) c = MM::mma(a.v[kk], bx[kk], c);
       return c;
@@ -300,7 +390,7 @@ __device__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__res
       if (p) load_x(p0, bx);
       for (int rt = wave; rt < nrt; rt += kLuWaves) {
         acc c = load_c(rt, p0);
-        if (p) c = update(rt, bx, c);
+        if (p) c = update(load_f(rt), bx, c);
 #pragma unroll
         for (int r = 0; r < 4; ++r) P[(rt * 16 + MM::row(r, kq)) * LS + jl] = c[r];
       }
@@ -311,18 +401,18 @@ __device__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__res
       int res = 0;
       // as few rows a lane as hold the slots in use, before and after
       const int rr = (min(nslot, cnt + (BAND ? h1 - h0 : 0)) + 63) >> 6;
-#define FSI_LU_CASE(R) \
-  if constexpr (R <= RMAX) { \
-    res = lu_factor<T, R, BAND>(A, ld, p, w, cnt, h0, h1, L, perm, plo); \
+#define FSI_LU_CASE(R, NC)                                                              \
+  if constexpr (R <= RMAX) {                                                            \
+    res = lu_factor<T, R, NC, BAND, PB>(A, ld, p, w, cnt, h0, h1, L, perm, plo);        \
   }
-      if (rr <= 1) { FSI_LU_CASE(1) }
-      else if (rr == 2) { FSI_LU_CASE(2) }
-      else if (rr == 3) { FSI_LU_CASE(3) }
-      else if (rr == 4) { FSI_LU_CASE(4) }
-      else if (rr == 5) { FSI_LU_CASE(5) }
-      else if (rr == 6) { FSI_LU_CASE(6) }
-      else if (rr <= 9) { FSI_LU_CASE(9) }
-      else { FSI_LU_CASE(13) }
+      // groups of as many columns as R rows a lane leave registers for
+      constexpr bool kDouble = sizeof(T) == 8;
+      if (rr <= 1) { FSI_LU_CASE(1, 16) }
+      else if (rr == 2) { FSI_LU_CASE(2, 16) }
+      else if (rr <= 4) { FSI_LU_CASE(4, 16) }
+      else if (rr <= 6) { FSI_LU_CASE(6, (kDouble ? 8 : 16)) }
+      else if (rr <= 8) { FSI_LU_CASE(8, (kDouble || RMAX > 8 ? 8 : 16)) }
+      else { FSI_LU_CASE(13, 4) }
 #undef FSI_LU_CASE
       if (lane == 0) *L.result(p) = res;
     } else if (p) {
@@ -335,14 +425,24 @@ __device__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__res
         T bx[4];
         load_x(c0, bx);
         acc ring[kLuAhead];
+        Quad<T> fr[PB == 1 ? kLuAhead : 1];
 #pragma unroll
-        for (int u = 0; u < kLuAhead; ++u) ring[u] = load_c(min(u, nrt - 1), c0);
+        for (int u = 0; u < kLuAhead; ++u) {
+          ring[u] = load_c(min(u, nrt - 1), c0);
+          if constexpr (PB == 1) fr[u] = load_f(min(u, nrt - 1));
+        }
         for (int rt0 = 0; rt0 < nrt; rt0 += kLuAhead) {
 #pragma unroll
           for (int u = 0; u < kLuAhead; ++u) {
             const int rt = rt0 + u;
             if (rt < nrt) {
-              const acc c = update(rt, bx, ring[u]);
+              acc c;
+              if constexpr (PB == 1) {
+                c = update(fr[u], bx, ring[u]);
+                fr[u] = load_f(min(rt + kLuAhead, nrt - 1));
+              } else {
+                c = update(load_f(rt), bx, ring[u]);
+              }
               ring[u] = load_c(min(rt + kLuAhead, nrt - 1), c0);
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
@@ -440,7 +540,7 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_band(double *__restrict__ A, 
                                                         int nslot, int *__restrict__ perm, int *__restrict__ plo,
                                                         int *__restrict__ status) {
   extern __shared__ __align__(16) unsigned char lu_lds[];
-  lu_matrix<double, RMAX, true>(A, n, ld, hi, cend, nslot, perm, plo, status, lu_lds);
+  lu_matrix<double, RMAX, true, 2>(A, n, ld, hi, cend, nslot, perm, plo, status, lu_lds);
 }
 
 // Rows of the inverse from the factors.  z A = e_i for 16 G unknowns i at a
@@ -460,10 +560,11 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_band(double *__restrict__ A, 
 // jhi(p): the end of the panels that its pivot rows reach.  prow: perm in
 // LDS, 16 np entries, clamped to n - 1.  The entries past n of every vector
 // are zero throughout (the matrix's columns past n are), so the clamped rows
-// contribute nothing.
+// contribute nothing.  pos: this lane's unknown in each 16-vector tile (a
+// negative one: none), the first ng <= G tiles hold any.
 template <typename T, int TPW, int TA, int G, class JLo, class JHi>
 __device__ __forceinline__ void lu_rows(const T *__restrict__ A, int n, int ld, const int *prow,
-                                        const int (&pos)[G], int pstart, JLo jlo, JHi jhi, T *bc,
+                                        const int (&pos)[G], int ng, int pstart, JLo jlo, JHi jhi, T *bc,
                                         typename Mfma16<T>::acc (&x)[TPW][G]) {
   typedef Mfma16<T> MM;
   typedef typename MM::acc acc;
@@ -514,9 +615,11 @@ __device__ __forceinline__ void lu_rows(const T *__restrict__ A, int n, int ld, 
   };
   auto apply = [&](const T (&a)[4], const acc (&y)[G], acc (&z)[G]) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int g = 0; g < G; ++g)
+      if (g < ng) {
 #pragma unroll
-      for (int g = 0; g < G; ++g) z[g] = MM::mma(a[kk], y[g][kk], z[g]);
+        for (int kk = 0; kk < 4; ++kk) z[g] = MM::mma(a[kk], y[g][kk], z[g]);
+      }
   };
   // tile u of this wave (panel j) by panel p, whose tiles in reach start at j0
   auto apply_tile = [&](int u, int p, int j0, const T (&a)[TA][4], const acc (&y)[G]) {
@@ -553,7 +656,7 @@ __device__ __forceinline__ void lu_rows(const T *__restrict__ A, int n, int ld, 
   };
   // with registers to spare the next panel's tiles are loaded during this
   // one's products, else after them
-  constexpr bool kAhead = TPW <= 9;
+  constexpr bool kAhead = TPW * G * (int)sizeof(T) <= 96;
   T a[TA][4], an[kAhead ? TA : 1][4];
 #pragma unroll
   for (int i = 0; i < TA; ++i)
@@ -597,7 +700,8 @@ __device__ __forceinline__ void lu_rows(const T *__restrict__ A, int n, int ld, 
       if (p + 2 < np) load_tiles(p + 1, p + 2, jhn, an);
 #pragma unroll
     for (int u = 0; u < TPW; ++u)
-      if (wave + kLuWaves * u > p + 1 && wave + kLuWaves * u < jh) apply_tile(u, p, p + 1, a, y);
+      if (wave + kLuWaves * u > p + 1 && wave + kLuWaves * u < jh) 
+        apply_tile(u, p, p + 1, a, y);
     jh = jhn;
     if constexpr (!kAhead)
       if (p + 2 < np) load_tiles(p + 1, p + 2, jhn, a);
@@ -626,7 +730,8 @@ __device__ __forceinline__ void lu_rows(const T *__restrict__ A, int n, int ld, 
       if (p > 1) load_tiles(p - 1, j0n, p - 1, an);
 #pragma unroll
     for (int u = 0; u < TPW; ++u)
-      if (wave + kLuWaves * u < p - 1 && wave + kLuWaves * u >= j0) apply_tile(u, p, j0, a, y);
+      if (wave + kLuWaves * u < p - 1 && wave + kLuWaves * u >= j0) 
+        apply_tile(u, p, j0, a, y);
     j0 = j0n;
     if constexpr (!kAhead)
       if (p > 1) load_tiles(p - 1, j0n, p - 1, a);
@@ -653,7 +758,7 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_band_rows(const double *__res
   __shared__ double bc[2 * 256];
   __shared__ int prow[TPW * kLuWaves * kLuNb];
   if (status[0]) return;
-  for (int s = threadIdx.x; s < TPW * kLuWaves * kLuNb; s += kLuThreads) prow[s] = perm[min(s, n - 1)];
+  for (int s = threadIdx.x; s < TPW * kLuWaves * kLuNb; s += kLuThreads) prow[s] = min(max(perm[min(s, n - 1)], 0), n - 1);
   __syncthreads();
   const int lane = threadIdx.x & 63, jl = lane & 15, kq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -661,7 +766,7 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_band_rows(const double *__res
   const int pos[1] = {b * kLuNb + jl};
   dx4 x[TPW][1];
   lu_rows<double, TPW, TA, 1>(
-      A, n, ld, prow, pos, b, [&](int p) { return plo[p]; }, [&](int p) { return (cend[p] + kLuNb - 1) / kLuNb; },
+      A, n, ld, prow, pos, 1, b, [&](int p) { return plo[p]; }, [&](int p) { return (cend[p] + kLuNb - 1) / kLuNb; },
       bc, x);
   if (pos[0] >= n) return;
   const int k = coldof[pos[0]], ec = col_exp(cmax, n0, k, kEquilSteps);
@@ -689,7 +794,7 @@ __global__ __launch_bounds__(256) void k_coarse_border(int n, const int *__restr
 
 template <int RMAX>
 static void launch_band_factor(double *A, const BandView &B, int64_t ld, int *status, hipStream_t st) {
-  const size_t shm = lu_lds_bytes(B.nslot, sizeof(double), kLuStride<double>);
+  const size_t shm = lu_lds_bytes<double>(B.nslot, 2);
   k_lu_band<RMAX><<<1, kLuThreads, shm, st>>>(A, B.n, ld, B.hi, B.cend, B.nslot, B.perm, B.plo, status);
 }
 template <int TPW, int TA>
@@ -703,14 +808,14 @@ static void launch_band_rows(const double *A, const BandView &B, int64_t ld, con
 template <int RMAX>
 static void allow_band_lds() {
   (void)hipFuncSetAttribute((const void *)k_lu_band<RMAX>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lu_lds_bytes(64 * RMAX, sizeof(double), kLuStride<double>));
+                            (int)lu_lds_bytes<double>(std::min(64 * RMAX, kLuBandSlots), 2));
 }
 void lu_coarse_prepare() {
   static std::once_flag once;   // setup threads may come together
   std::call_once(once, [] {
     allow_band_lds<2>();
     allow_band_lds<4>();
-    allow_band_lds<5>();
+    allow_band_lds<6>();
   });
 }
 
@@ -728,7 +833,7 @@ void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &
   else if (B.nslot <= 256)
     launch_band_factor<4>(A, B, ld, status, st);
   else
-    launch_band_factor<5>(A, B, ld, status, st);
+    launch_band_factor<6>(A, B, ld, status, st);
   const int np = (B.n + kLuNb - 1) / kLuNb, tpw = (np + kLuWaves - 1) / kLuWaves;
   if (tpw <= 4)
     launch_band_rows<4, 4>(A, B, ld, status, cs.n, C0, st);
@@ -738,6 +843,262 @@ void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &
     launch_band_rows<20, 3>(A, B, ld, status, cs.n, C0, st);
   launch_coarse_diagonal(cs, B.n, status, st);
   k_coarse_border<<<dim3((cs.n + 255) / 256, cs.n), 256, 0, st>>>(cs.n, cs.fpos, cs.rowptr, cs.val, C0);
+}
+
+// ------------------------------------------------------------------ Schwarz blocks
+// Rows of a level's operator scaled by powers of two to a largest entry in
+// [1/2, 1), for the extraction of its blocks: with the equations of both
+// materials in one block, pivots chosen by unscaled magnitudes lose digits
+// (a time step's interface block of 336 dofs: error of the inverse 9e-12, and
+// 9e-14 scaled).  er: the rows' exponents.  One row per 16 lanes.
+template <typename T>
+__global__ __launch_bounds__(256) void k_scale_rows(int n, const int *__restrict__ rowptr,
+                                                    const double *__restrict__ val, T *__restrict__ out,
+                                                    int *__restrict__ er) {
+  const int r = blockIdx.x * 16 + (threadIdx.x >> 4), sub = threadIdx.x & 15;
+  if (r >= n) return;
+  const int p0 = rowptr[r], p1 = rowptr[r + 1];
+  int top = 0;   // the largest biased exponent of a finite entry
+#pragma unroll 4
+  for (int p = p0 + sub; p < p1; p += 16) {
+    const int b = (int)((__double_as_longlong(val[p]) >> 52) & 0x7ff);
+    top = max(top, b == 0x7ff ? 0 : b);
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) top = max(top, __shfl_xor(top, o));
+  const int e = top ? 1022 - top : 0;
+  if (sub == 0) er[r] = e;
+#pragma unroll 4
+  for (int p = p0 + sub; p < p1; p += 16) out[p] = (T)ldexp(val[p], e);
+}
+
+// One workgroup per block, the largest first.  Up to 372 dofs (336 blocks, more
+// than compute units) it is bound by the updates' traffic: 4.9 GB in 1.15 ms in
+// FP64, 4.2 TB/s, a plain copy's rate; one block alone takes 0.39 ms, the chain
+// of pivot steps (0.75 us each at six rows a lane).  Larger blocks (one
+// workgroup to a compute unit) are bound by that chain.
+template <typename T, int RMAX, int PB>
+__global__ __launch_bounds__(kLuThreads) void k_lu_blocks(T *__restrict__ blocks, const int64_t *__restrict__ boff,
+                                                          const int *__restrict__ pm,
+                                                          const int64_t *__restrict__ poff,
+                                                          int *__restrict__ perm, int *__restrict__ status,
+                                                          const int *__restrict__ order) {
+  extern __shared__ __align__(16) unsigned char lu_lds[];
+  const int k = order[blockIdx.x], m = pm[k], ld = block_ld(m);
+  lu_matrix<T, RMAX, false, PB>(blocks + boff[k], m, ld, nullptr, nullptr, ld, perm + poff[k], nullptr, status + k,
+                            lu_lds);
+}
+
+// Rows of the inverses in the Schwarz kernels' layout: one workgroup per task
+// (a block, up to 64 rows of its inverse), written column by column (entry
+// (c, r) of a task of nr rows at c nr + r), which is how the rows' 16-vector
+// tiles come out: 16 rows of one column side by side in 16 lanes; the scales
+// of the blocks' rows go into the inverse's columns.  cscale
+// (with 16-bit storage): the largest magnitude of every column over the
+// block's rows, as float bits.  The tasks of one XCD are consecutive, so a
+// block's factors stay in its L2 for all of its tasks.
+template <typename T, int TPW, int G>
+__global__ __launch_bounds__(kLuThreads) void k_lu_rows(LuRowsBatch<T> B, int ntask, int chunk) {
+  typedef Mfma16<T> MM;
+  __shared__ T bc[2 * G * 256];
+  __shared__ int prow[TPW * kLuWaves * kLuNb], scale[TPW * kLuWaves * kLuNb];
+  const int task = (blockIdx.x & 7) * chunk + (blockIdx.x >> 3);
+  if (task >= ntask) return;
+  int e = 0;
+  while (e + 1 < B.count && task >= B.task0[e + 1]) ++e;
+  const LuRowsItem<T> &it = B.it[e];
+  const int t = task - B.task0[e];
+  const int lane = threadIdx.x & 63, jl = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k = it.task_patch[t], r0 = it.task_row0[t], m = it.pm[k];
+  const int nr = min(64, it.po[k] - r0);
+  const int *local = it.row_local + it.row_off[k] + r0;
+  const int *perm = it.perm + it.pdof_off[k];
+  for (int s = threadIdx.x; s < TPW * kLuWaves * kLuNb; s += kLuThreads) {
+    const int c = min(max(perm[min(s, m - 1)], 0), m - 1);
+    prow[s] = c;
+    scale[s] = it.er ? it.er[it.dof[it.pdof_off[k] + c]] : 0;
+  }
+  T *W = it.W + it.woff[k] + (int64_t)r0 * m;
+  __syncthreads();
+  const int first = local[0];   // the rows are in ascending order
+  for (int v0 = 0; v0 < nr; v0 += 16 * G) {
+    int pos[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int r = v0 + 16 * g + jl;
+      pos[g] = r < nr ? local[r] : -1;
+    }
+    typename MM::acc x[TPW][G];
+    lu_rows<T, TPW, TPW, G>(
+        it.blocks + it.boff[k], m, block_ld(m), prow, pos, min(G, (nr - v0 + 15) / 16), (v0 ? local[v0] : first) / kLuNb,
+        [](int) { return 0; }, [&](int) { return m; }, bc, x);
+#pragma unroll
+    for (int u = 0; u < TPW; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int s = (wave + kLuWaves * u) * kLuNb + MM::row(r, kq);
+        if (s < m) {
+          const int c = prow[s], er = scale[s];
+          float top = 0.f;
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const int i = v0 + 16 * g + jl;
+            if (i < nr) {
+              const T y = ldexp(x[u][g][r], er);
+              W[(int64_t)c * nr + i] = y;
+              top = fmaxf(top, fabsf((float)y));
+            }
+          }
+          if (it.cscale) {
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+            if (jl == 0) atomicMax(reinterpret_cast<unsigned *>(it.cscale + it.pdof_off[k]) + c, __float_as_uint(top));
+          }
+        }
+      }
+    __syncthreads();
+  }
+}
+
+// 16-bit copy of the rows that k_lu_rows left in FP32, one workgroup per
+// task: row r is stored divided by the column scales and by its row scale,
+// the largest |w| / cs[c] of the row, in the grouped layout (see
+// launch_pack_owned), or without woff16 in the plain one.  Lane r of every
+// wave holds row r, the waves share the columns; in the grouped layout four
+// columns make one 8-byte store a lane.
+template <int KIND>
+__global__ __launch_bounds__(256) void k_pack16_rows(const float *__restrict__ rows, const int *__restrict__ pm,
+                                                     const int *__restrict__ po, const int *__restrict__ row_off,
+                                                     const int64_t *__restrict__ pdof_off,
+                                                     const int64_t *__restrict__ woff,
+                                                     const int64_t *__restrict__ woff16,
+                                                     const int *__restrict__ task_patch,
+                                                     const int *__restrict__ task_row0,
+                                                     const float *__restrict__ cscale, uint16_t *__restrict__ W16,
+                                                     float *__restrict__ wscale) {
+  __shared__ double part[4][64];
+  const int k = task_patch[blockIdx.x], r0 = task_row0[blockIdx.x], m = pm[k];
+  const int nr = min(64, po[k] - r0), r = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rc = min(r, nr - 1);
+  const float *W = rows + woff[k] + (int64_t)r0 * m + rc, *cs = cscale + pdof_off[k];
+  double top = 0.0;
+#pragma unroll 8
+  for (int c = wave; c < m; c += 4) top = fmax(top, fabs((double)W[c * nr]) / (double)cs[c]);
+  part[wave][r] = top;
+  __syncthreads();
+  top = fmax(fmax(part[0][r], part[1][r]), fmax(part[2][r], part[3][r]));
+  if (top == 0.0) top = 1.0;
+  if (r >= nr) return;
+  if (wave == 0) wscale[row_off[k] + r0 + r] = (float)top;
+  auto rounded = [&](int c) -> uint16_t {
+    if (c >= m) return 0;
+    const float v = (float)((double)W[c * nr] / ((double)cs[c] * top));
+    if constexpr (KIND == 1) {
+      const __hip_bfloat16 b = __float2bfloat16(v);
+      return *reinterpret_cast<const uint16_t *>(&b);
+    } else {
+      const __half b = __float2half(v);
+      return *reinterpret_cast<const uint16_t *>(&b);
+    }
+  };
+  if (!woff16) {
+    uint16_t *out = W16 + woff[k] + (int64_t)r0 * m + r;
+    for (int c = wave; c < m; c += 4) out[c * nr] = rounded(c);
+    return;
+  }
+  const int m4 = (m + 3) & ~3;
+  uint16_t *out = W16 + woff16[k] + (int64_t)r0 * m4 + 4 * r;
+#pragma unroll 2
+  for (int c = 4 * wave; c < m; c += 16) {
+    ushort4 q;
+    q.x = rounded(c), q.y = rounded(c + 1), q.z = rounded(c + 2), q.w = rounded(c + 3);
+    *reinterpret_cast<ushort4 *>(out + (c / 4) * 4 * nr) = q;
+  }
+}
+
+template <typename T, int RMAX, int PB = 2>
+static void launch_blocks(T *blocks, const int64_t *boff, const int *pm, const int64_t *poff, int *perm, int *status,
+                          const int *order, int nblk, int mmax, hipStream_t st, hipEvent_t ev0) {
+  const size_t shm = lu_lds_bytes<T>(block_ld(mmax), PB);
+  (void)hipFuncSetAttribute((const void *)k_lu_blocks<T, RMAX, PB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)shm);
+  hipExtLaunchKernelGGL((k_lu_blocks<T, RMAX, PB>), dim3(nblk), dim3(kLuThreads), shm, st, ev0, nullptr, 0, blocks,
+                        boff, pm, poff, perm, status, order);
+}
+template <typename T>
+void launch_lu_blocks(T *blocks, const int64_t *boff, const int *pm, const int64_t *poff, int *perm, int *status,
+                      const int *order, int nblk, int mmax, hipStream_t st, hipEvent_t ev0) {
+  if (nblk == 0) return;
+  // rows a lane of the factoring wave: registers for the largest block; two
+  // panels of more than 512 FP64 rows do not fit in LDS
+  if (mmax <= 128)
+    launch_blocks<T, 2>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
+  else if (mmax <= 256)
+    launch_blocks<T, 4>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
+  else if (mmax <= 384)
+    launch_blocks<T, 6>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
+  else if (mmax <= 512)
+    launch_blocks<T, 8>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
+  else
+    launch_blocks<T, 13, sizeof(T) == 8 ? 1 : 2>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
+}
+template void launch_lu_blocks<double>(double *, const int64_t *, const int *, const int64_t *, int *, int *,
+                                       const int *, int, int, hipStream_t, hipEvent_t);
+template void launch_lu_blocks<float>(float *, const int64_t *, const int *, const int64_t *, int *, int *,
+                                      const int *, int, int, hipStream_t, hipEvent_t);
+
+template <typename T>
+void launch_lu_rows(const LuRowsItem<T> *items, const int *ntasks, int count, int mmax, hipStream_t st,
+                    hipEvent_t ev1) {
+  for (int i0 = 0; i0 < count; i0 += kLuRowsItems) {
+    LuRowsBatch<T> B;
+    B.count = std::min(count - i0, kLuRowsItems);
+    B.task0[0] = 0;
+    for (int i = 0; i < B.count; ++i) {
+      B.it[i] = items[i0 + i];
+      B.task0[i + 1] = B.task0[i] + ntasks[i0 + i];
+    }
+    const int ntask = B.task0[B.count], chunk = (ntask + 7) / 8;
+    if (ntask == 0) continue;
+    const hipEvent_t ev = i0 + kLuRowsItems >= count ? ev1 : nullptr;
+#define FSI_LU_ROWS(TPW, G)                                                                                  \
+  hipExtLaunchKernelGGL((k_lu_rows<T, TPW, G>), dim3(8 * chunk), dim3(kLuThreads), 0, st, nullptr, ev, 0, B, \
+                        ntask, chunk)
+    // panels a wave: registers for the largest block
+    if (mmax <= 128)
+      FSI_LU_ROWS(1, 4);
+    else if (mmax <= 256)
+      FSI_LU_ROWS(2, 4);
+    else if (mmax <= 384)
+      FSI_LU_ROWS(3, 4);
+    else if (mmax <= 512)
+      FSI_LU_ROWS(4, (sizeof(T) == 8 ? 2 : 4));
+    else
+      FSI_LU_ROWS(7, (sizeof(T) == 8 ? 2 : 4));
+#undef FSI_LU_ROWS
+  }
+}
+template void launch_lu_rows<double>(const LuRowsItem<double> *, const int *, int, int, hipStream_t, hipEvent_t);
+template void launch_lu_rows<float>(const LuRowsItem<float> *, const int *, int, int, hipStream_t, hipEvent_t);
+
+template <typename T>
+void launch_scale_rows(const CsrView<double> &J, T *out, int *er, hipStream_t st) {
+  if (J.nrows > 0) k_scale_rows<T><<<(J.nrows + 15) / 16, 256, 0, st>>>(J.nrows, J.rowptr, J.val, out, er);
+}
+template void launch_scale_rows<double>(const CsrView<double> &, double *, int *, hipStream_t);
+template void launch_scale_rows<float>(const CsrView<double> &, float *, int *, hipStream_t);
+
+void launch_pack16_rows(const float *rows, const int *pm, const int *po, const int *row_off, const int64_t *pdof_off,
+                        const int64_t *woff, const int64_t *woff16, const int *task_patch, const int *task_row0,
+                        int ntask, const float *cscale, uint16_t *W16, int w16_kind, float *wscale, hipStream_t st) {
+  if (ntask == 0) return;
+  if (w16_kind == 1)
+    k_pack16_rows<1><<<ntask, 256, 0, st>>>(rows, pm, po, row_off, pdof_off, woff, woff16, task_patch, task_row0,
+                                            cscale, W16, wscale);
+  else
+    k_pack16_rows<2><<<ntask, 256, 0, st>>>(rows, pm, po, row_off, pdof_off, woff, woff16, task_patch, task_row0,
+                                            cscale, W16, wscale);
 }
 
 }  // namespace fsi

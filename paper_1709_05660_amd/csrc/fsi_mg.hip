@@ -329,7 +329,7 @@ static void build_patch_layout(Level &L, const fsi_patches &P, const fsi_csr &J,
     woff16[k] = wmain16;
     if (!is_ilu) wcls += (int64_t)o * pm[k];
     if (!is_ilu && !solid) wmain16 += (int64_t)o * ((pm[k] + 3) & ~3);
-    boff[k + 1] = boff[k] + (int64_t)pm[k] * pm[k];
+    boff[k + 1] = boff[k] + ((int64_t)pm[k] * block_ld(pm[k]) + 15) / 16 * 16;
     for (int i = 0; i < pm[k]; ++i) {
       row_patch.push_back(k);
       row_local.push_back(i);
@@ -455,7 +455,7 @@ static void build_patch_layout(Level &L, const fsi_patches &P, const fsi_csr &J,
     L.rhoref = dalloc<float>(full_off[np], own);
   }
   // extraction map: one slot per CSR entry of every block row
-  if (L.boff_total >= ((int64_t)1 << 31))
+  if (L.sum_m2 >= ((int64_t)1 << 31) || L.boff_total >= ((int64_t)1 << 32) - 1)
     throw Error(FSI_E_INVALID, "the blocks of one level exceed 2^31 entries");
   if (!ilu_patch.empty()) {
     // each ILU block's pattern (J's stored entries in the block, and the
@@ -489,7 +489,7 @@ static void build_patch_layout(Level &L, const fsi_patches &P, const fsi_csr &J,
         for (int c : row_cols) {
           const int64_t bit = (int64_t)i * m + c;
           mk[bit >> 5] |= 1u << (bit & 31);
-          const int pos = (int)(L.h_boff[k] + (int64_t)i * m + c);
+          const int pos = (int)(unsigned)(L.h_boff[k] + (int64_t)i * block_ld(m) + c);
           if (c < i) {
             lcol.push_back((int16_t)c);
             lpos.push_back(pos);
@@ -569,6 +569,7 @@ static void build_patch_layout(Level &L, const fsi_patches &P, const fsi_csr &J,
     slot_off[t + 1] = slot_off[t] + (J.rowptr[g + 1] - J.rowptr[g]);
   }
   L.ext_nslots = slot_off.back();
+  L.row_exp = dalloc<int>(L.n, own);
   L.d_ext_slot_off = dupload(slot_off.data(), (int64_t)slot_off.size(), own, st);
   L.d_ext_src = dalloc<int>(L.ext_nslots, own);
   L.d_ext_dst = dalloc<int>(L.ext_nslots, own);
@@ -695,10 +696,8 @@ static void free_list(DevList &owned) {
   while (!owned.v.empty()) free_one(owned, owned.v.size() - 1);
 }
 
-// owned rows of every block inverse in the storage precision of the level
-// (the inverted blocks of level L sit at mg.blk_scratch + L.blk_base)
-template <typename TB>
-static void pack_level_t(MG &mg, Level &L, const TB *B, hipStream_t st) {
+// storage of the owned rows of a level's block inverses, allocated once
+static void ensure_rows(MG &mg, Level &L, hipStream_t st) {
   const int prec = mg.opts.precision;
   if (prec == FSI_PREC_FP64) {
     if (!L.W64) L.W64 = dalloc<double>(L.woff_total, mg.owned);
@@ -706,7 +705,7 @@ static void pack_level_t(MG &mg, Level &L, const TB *B, hipStream_t st) {
     if (!L.W32) L.W32 = dalloc<float>(L.woff_total, mg.owned);
   } else {
     if (!L.W16) {
-      // the grouped layout's padding columns stay zero (the packer never writes them)
+      // the grouped layout's padding columns stay zero
       L.W16 = dalloc<uint16_t>(std::max<int64_t>(L.woff16_total, 1), mg.owned);
       hip_check(hipMemsetAsync(L.W16, 0, sizeof(uint16_t) * std::max<int64_t>(L.woff16_total, 1), st),
                 "clear 16-bit storage");
@@ -714,41 +713,59 @@ static void pack_level_t(MG &mg, Level &L, const TB *B, hipStream_t st) {
       L.Cscale = dalloc<float>(L.sum_m, mg.owned);
     }
     L.w16_kind = prec == FSI_PREC_MIXED_BF16 ? 1 : 2;
+  }
+  if (L.ntask_s && !L.Ws) L.Ws = dalloc<float>(L.woff_solid, mg.owned);
+}
+
+// The blocks are extracted from operators with scaled rows (launch_scale_rows),
+// but for ILU blocks, which are factored as they are.
+static bool blocks_scaled(const MG &mg) { return mg.opts.fluid_ilu == 0; }
+
+static void ensure_full16(MG &mg, Level &L) {
+  if (L.Wfull16) return;
+  L.Wfull16 = dalloc<uint16_t>(L.wfull_total, mg.owned);
+  L.Wscale_full = dalloc<float>(L.full_rows, mg.owned);
+}
+
+// owned rows of every block inverse in the storage precision of the level
+// (the inverted blocks of level L sit at mg.blk_scratch + L.blk_base)
+template <typename TB>
+static void pack_level_t(MG &mg, Level &L, const TB *B, hipStream_t st) {
+  const int prec = mg.opts.precision;
+  const int *er = blocks_scaled(mg) ? L.row_exp : nullptr;
+  ensure_rows(mg, L, st);
+  if (prec != FSI_PREC_FP64 && prec != FSI_PREC_MIXED_FP32) {
     // column scales of the owned rows, and of every row of the refined
     // blocks when they are kept in 16 bits (one scale array, disjoint columns)
     const bool full16 = L.nftask && mg.opts.solid_precision != FSI_PREC_MIXED_FP32;
     launch_colscale(B, L.d_boff, L.d_pm, L.d_po, L.d_out_off, L.d_own_local, L.d_pdof_off,
                     L.d_task_patch, L.d_task_row0, L.ntask, L.sum_m, L.Cscale, mg.gj_perm + L.pm_base,
-                    L.mmax, st, true, !full16);
+                    L.d_dof, er, L.mmax, st, true, !full16);
     if (full16)
       launch_colscale(B, L.d_boff, L.d_pm, L.d_po_full, L.d_full_off, L.d_full_local, L.d_pdof_off,
                       L.d_ftask_patch, L.d_ftask_row0, L.nftask, L.sum_m, L.Cscale,
-                      mg.gj_perm + L.pm_base, L.mmax, st, false, true);
+                      mg.gj_perm + L.pm_base, L.d_dof, er, L.mmax, st, false, true);
   }
   launch_pack_owned(B, L.d_boff, L.d_pm, L.d_po, L.d_woff, L.d_out_off, L.d_own_local,
                     L.d_task_patch, L.d_task_row0, L.ntask, L.W64, L.W32, L.W16, L.w16_kind,
-                    L.Wscale, L.d_pdof_off, L.Cscale, mg.gj_perm + L.pm_base, L.d_woff16, st);
+                    L.Wscale, L.d_pdof_off, L.Cscale, mg.gj_perm + L.pm_base, L.d_woff16, L.d_dof, er, st);
   if (L.ntask_s) {   // solid blocks' owned rows in FP32
-    if (!L.Ws) L.Ws = dalloc<float>(L.woff_solid, mg.owned);
     launch_pack_owned(B, L.d_boff, L.d_pm, L.d_po, L.d_woff, L.d_out_off, L.d_own_local,
                       L.d_task_patch_s, L.d_task_row0_s, L.ntask_s, (double *)nullptr, L.Ws,
                       (uint16_t *)nullptr, 0, (float *)nullptr, L.d_pdof_off, (const float *)nullptr,
-                      mg.gj_perm + L.pm_base, (const int64_t *)nullptr, st);
+                      mg.gj_perm + L.pm_base, (const int64_t *)nullptr, L.d_dof, er, st);
   }
   if (L.nftask) {    // refined solid blocks: every row of the inverse, FP32 or 16-bit
     const bool full16 = prec != FSI_PREC_MIXED_FP32 && mg.opts.solid_precision != FSI_PREC_MIXED_FP32;
     if (full16) {
-      if (!L.Wfull16) {
-        L.Wfull16 = dalloc<uint16_t>(L.wfull_total, mg.owned);
-        L.Wscale_full = dalloc<float>(L.full_rows, mg.owned);
-      }
+      ensure_full16(mg, L);
     } else if (!L.Wfull32) {
       L.Wfull32 = dalloc<float>(L.wfull_total, mg.owned);
     }
     launch_pack_owned(B, L.d_boff, L.d_pm, L.d_po_full, L.d_woff_full, L.d_full_off, L.d_full_local,
                       L.d_ftask_patch, L.d_ftask_row0, L.nftask, (double *)nullptr, full16 ? nullptr : L.Wfull32,
                       full16 ? L.Wfull16 : nullptr, L.w16_kind, L.Wscale_full, L.d_pdof_off,
-                      full16 ? L.Cscale : nullptr, mg.gj_perm + L.pm_base, (const int64_t *)nullptr, st);
+                      full16 ? L.Cscale : nullptr, mg.gj_perm + L.pm_base, (const int64_t *)nullptr, L.d_dof, er, st);
   }
   hip_check(hipGetLastError(), "pack launch");
 }
@@ -831,21 +848,28 @@ static void enqueue_coarse(MG &mg, Level &L, hipStream_t st) {
 // B_k = J_l[I_k, I_k] of every smoothing level into the setup scratch: FP64
 // blocks, or FP32 working matrices for the mixed forms (the same element
 // offsets, the buffer read as floats)
-static void extract_blocks(MG &mg, hipStream_t st) {
-  if (mg.mixed) {
-    float *B = reinterpret_cast<float *>(mg.blk_scratch);
+template <typename T>
+static void extract_blocks_t(MG &mg, T *B, hipStream_t st) {
+  if constexpr (sizeof(T) == 8)
+    launch_fill_f64(B, mg.blk_total, 0.0, st);
+  else
     launch_fill_f32(B, mg.blk_total, 0.0f, st);
-    for (int l = 1; l < mg.nlevels; ++l) {
-      Level &L = mg.lv[l];
-      launch_extract(L.J.val, L.ext_nslots, L.d_ext_src, L.d_ext_dst, B + L.blk_base, st);
-    }
-  } else {
-    launch_fill_f64(mg.blk_scratch, mg.blk_total, 0.0, st);
-    for (int l = 1; l < mg.nlevels; ++l) {
-      Level &L = mg.lv[l];
-      launch_extract(L.J.val, L.ext_nslots, L.d_ext_src, L.d_ext_dst, mg.blk_scratch + L.blk_base, st);
+  T *val = reinterpret_cast<T *>(mg.scaled_val);
+  for (int l = 1; l < mg.nlevels; ++l) {
+    Level &L = mg.lv[l];
+    if (blocks_scaled(mg)) {
+      launch_scale_rows<T>(L.J.v64(), val, L.row_exp, st);
+      launch_extract<T, T>(val, L.ext_nslots, L.d_ext_src, L.d_ext_dst, B + L.blk_base, st);
+    } else {
+      launch_extract<double, T>(L.J.val, L.ext_nslots, L.d_ext_src, L.d_ext_dst, B + L.blk_base, st);
     }
   }
+}
+static void extract_blocks(MG &mg, hipStream_t st) {
+  if (mg.mixed)
+    extract_blocks_t(mg, reinterpret_cast<float *>(mg.blk_scratch), st);
+  else
+    extract_blocks_t(mg, mg.blk_scratch, st);
 }
 
 // the batched Gauss-Jordan inversion of every block (FP64, or FP32 for the mixed forms)
@@ -885,6 +909,97 @@ static void invert_large(MG &mg, hipStream_t st) {
   hip_check(hipGetLastError(), "large block launch");
 }
 
+// LU inversion of the blocks where none is left to the Gauss-Jordan chain of
+// large blocks, unless the autotuner chose a Gauss-Jordan variant: the pivot
+// search needs no workgroup barrier, a third of the entries is updated, and
+// only the rows the V-cycle uses are formed.  Factors and packed rows against
+// the best Gauss-Jordan variant with packing: 336 blocks of the 128x32 system
+// (up to 372 dofs) 1.15 + 0.67 ms against 3.05 + 0.32 in FP64, 0.74 + 0.37 +
+// 0.14 (16-bit) against 2.24 + 0.36 in FP32; 288 blocks of the 32x8x8 system
+// (up to 637 dofs) in FP32 4.1 + 1.1 + 0.2 against 9.5 + 0.7; the 32 of
+// 16x4x4 (FP64, up to 490) 1.15 + 0.25 against 2.7 + 0.1.
+static bool lu_possible(const MG &mg) {
+  return mg.large.empty() && mg.lu_nblk > 0;
+}
+static bool lu_chosen(const MG &mg) {
+  return lu_possible(mg) && (mg.gj_variant == kGjAuto || mg.gj_variant == kLu64 || mg.gj_variant == kLu32);
+}
+
+// factors every block in place and writes the rows that the V-cycle uses
+template <typename T>
+static void lu_invert_t(MG &mg, T *B, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  launch_lu_blocks<T>(B, mg.all_boff, mg.all_pm, mg.all_poff, mg.gj_perm, mg.status, mg.lu_order, mg.lu_nblk,
+                      mg.mmax_all, st, ev0);
+  const bool is16 = mg.opts.precision == FSI_PREC_MIXED_BF16 || mg.opts.precision == FSI_PREC_MIXED_FP16;
+  const bool full16 = is16 && mg.opts.solid_precision != FSI_PREC_MIXED_FP32;   // refined blocks in 16 bits too
+  // rows to be kept in 16 bits go through the half of the scratch that FP32 blocks leave free
+  auto rows32 = [&](const Level &L) { return B + mg.blk_total + 64 + L.blk_base; };
+  std::vector<LuRowsItem<T>> items;
+  std::vector<int> ntasks;
+  for (int l = mg.nlevels - 1; l >= 1; --l) {   // the finest level's tasks first
+    Level &L = mg.lv[l];
+    ensure_rows(mg, L, st);
+    LuRowsItem<T> it{};
+    it.blocks = B + L.blk_base;
+    it.boff = L.d_boff;
+    it.pdof_off = L.d_pdof_off;
+    it.pm = L.d_pm;
+    it.perm = mg.gj_perm + L.pm_base;
+    it.dof = L.d_dof;
+    it.er = blocks_scaled(mg) ? L.row_exp : nullptr;
+    auto add = [&](T *W, const int64_t *woff, const int *po, const int *off, const int *local, const int *patch,
+                   const int *row0, int n, float *cscale) {
+      if (!n) return;
+      it.W = W;
+      it.woff = woff;
+      it.po = po;
+      it.row_off = off;
+      it.row_local = local;
+      it.task_patch = patch;
+      it.task_row0 = row0;
+      it.cscale = cscale;
+      items.push_back(it);
+      ntasks.push_back(n);
+    };
+    T *W;
+    if constexpr (sizeof(T) == 8)
+      W = L.W64;
+    else
+      W = is16 ? rows32(L) : L.W32;
+    if (is16) launch_fill_f32(L.Cscale, L.sum_m, 0.0f, st);
+    add(W, L.d_woff, L.d_po, L.d_out_off, L.d_own_local, L.d_task_patch, L.d_task_row0, L.ntask,
+        is16 ? L.Cscale : nullptr);
+    if constexpr (sizeof(T) == 4) {
+      add(L.Ws, L.d_woff, L.d_po, L.d_out_off, L.d_own_local, L.d_task_patch_s, L.d_task_row0_s, L.ntask_s, nullptr);
+      if (L.nftask && !full16 && !L.Wfull32) L.Wfull32 = dalloc<float>(L.wfull_total, mg.owned);
+      add(full16 ? rows32(L) + L.woff_total : L.Wfull32, L.d_woff_full, L.d_po_full, L.d_full_off, L.d_full_local,
+          L.d_ftask_patch, L.d_ftask_row0, L.nftask, full16 ? L.Cscale : nullptr);
+    }
+  }
+  launch_lu_rows<T>(items.data(), ntasks.data(), (int)items.size(), mg.mmax_all, st, ev1);
+  if constexpr (sizeof(T) == 4)
+    if (is16)
+      for (int l = mg.nlevels - 1; l >= 1; --l) {
+        Level &L = mg.lv[l];
+        launch_scale_fix(L.Cscale, L.sum_m, st);
+        launch_pack16_rows(rows32(L), L.d_pm, L.d_po, L.d_out_off, L.d_pdof_off, L.d_woff, L.d_woff16,
+                           L.d_task_patch, L.d_task_row0, L.ntask, L.Cscale, L.W16, L.w16_kind, L.Wscale, st);
+        if (full16 && L.nftask) {
+          ensure_full16(mg, L);
+          launch_pack16_rows(rows32(L) + L.woff_total, L.d_pm, L.d_po_full, L.d_full_off, L.d_pdof_off,
+                             L.d_woff_full, nullptr, L.d_ftask_patch, L.d_ftask_row0, L.nftask, L.Cscale, L.Wfull16,
+                             L.w16_kind, L.Wscale_full, st);
+        }
+      }
+  hip_check(hipGetLastError(), "LU launch");
+}
+static void lu_invert(MG &mg, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if (mg.mixed)
+    lu_invert_t(mg, reinterpret_cast<float *>(mg.blk_scratch), st, ev0, ev1);
+  else
+    lu_invert_t(mg, mg.blk_scratch, st, ev0, ev1);
+}
+
 // next event pair of a profiling list (created on first use)
 static hipEvent_t *prof_event_pair(std::vector<std::pair<hipEvent_t, hipEvent_t>> &evs, size_t &used) {
   if (used == evs.size()) {
@@ -915,6 +1030,7 @@ void refactor(MG &mg, hipStream_t st) {
       launch_cast_d2f(L.J.val, L.J.val32, L.J.nnz, st);
       if (L.nref) launch_gather_f32(L.J.val32, L.d_ref_src, L.ref_nnz, L.bref, st);   // refined blocks' B_k
     }
+  const bool lu = lu_chosen(mg);
   if (mg.nlevels > 1) extract_blocks(mg, st);
   hip_check(hipStreamWaitEvent(mg.side_stream, mg.ev_fork, 0), "fork wait");
   if (mg.opts.use_graph) {
@@ -933,11 +1049,15 @@ void refactor(MG &mg, hipStream_t st) {
   hip_check(hipEventRecord(mg.ev_join, mg.side_stream), "join");
   if (mg.nlevels > 1) {
     hipEvent_t *ev = mg.prof_on ? prof_event_pair(mg.prof_gj_ev, mg.prof_gj_used) : nullptr;
-    invert_blocks(mg, mg.gj_variant, st, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
-    hip_check(hipGetLastError(), "gj launch");
-    invert_large(mg, st);
+    if (lu) {
+      lu_invert(mg, st, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
+    } else {
+      invert_blocks(mg, mg.gj_variant, st, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
+      hip_check(hipGetLastError(), "gj launch");
+      invert_large(mg, st);
+    }
     for (int l = 1; l < mg.nlevels; ++l) {
-      pack_level(mg, mg.lv[l], st);
+      if (!lu) pack_level(mg, mg.lv[l], st);
       if (mg.mixed)
         ilu_factor_level(mg, mg.lv[l], l, reinterpret_cast<float *>(mg.blk_scratch) + mg.lv[l].blk_base, st);
       else
@@ -1644,9 +1764,18 @@ MG *mg_setup(const fsi_level *levels, int nlevels, const fsi_mg_opts *opts, hipS
       const std::vector<int> sched = gj_schedule(all_pm.data(), mg->npatch_all, mg->gj_grid);
       mg->gj_sched = dalloc<int>(2 * (int64_t)mg->npatch_all + 1, mg->owned);
       stage_copy(mg->gj_sched, sched.data(), sizeof(int) * sched.size(), st);
+      std::vector<int> order;
+      for (int k = 0; k < mg->npatch_all; ++k)
+        if (all_pm[k] > 0) order.push_back(k);
+      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return all_pm[a] > all_pm[b]; });
+      mg->lu_nblk = (int)order.size();
+      mg->lu_order = dupload(order.data(), mg->lu_nblk, mg->owned, st);
     }
     mg->gj_perm = dalloc<int>(std::max<int64_t>(pbase, 1), mg->owned);
     mg->gj_used = dalloc<int>(std::max<int64_t>(pbase, 1), mg->owned);
+    int64_t nnz_max = 1;
+    for (int l = 1; l < nlevels; ++l) nnz_max = std::max<int64_t>(nnz_max, levels[l].J.nnz);
+    mg->scaled_val = dalloc<double>(mg->mixed ? (nnz_max + 1) / 2 : nnz_max, mg->owned);
     // the blocks' statuses, then the coarsest operator's (one read-back)
     mg->status = dalloc<int>(mg->npatch_all + 1, mg->owned);
     mg->status0 = mg->status + mg->npatch_all;
@@ -1729,6 +1858,8 @@ void release_setup_scratch(MG &mg) {
   };
   drop(mg.blk_scratch);
   drop(mg.dense_scratch);
+  drop(mg.scaled_val);
+  mg.scaled_val = nullptr;
   mg.blk_scratch = nullptr;
   mg.dense_scratch = nullptr;
   for (Level &L : mg.lv) {
@@ -2227,11 +2358,13 @@ int autotune(MG &mg, const char *db_path, hipStream_t st) {
     // overlaps the batched launch there).  The schedule changes which
     // workgroup inverts a block, not the result.
     char key[256], gkey[256];
+    int64_t sum_m2 = 0;
+    for (const Level &L : mg.lv) sum_m2 += L.sum_m2;
     snprintf(key, sizeof key, "gj3:%s%d:%d:%lld", mg.mixed ? "f32:" : "", mg.mmax_all, mg.npatch_all,
-             (long long)mg.blk_total);
+             (long long)sum_m2);
     auto gj_key = [&](int var) {
       snprintf(gkey, sizeof gkey, "gjg:%s%d:%d:%lld:%d", mg.mixed ? "f32:" : "", mg.mmax_all,
-               mg.npatch_all, (long long)mg.blk_total, var);
+               mg.npatch_all, (long long)sum_m2, var);
       return std::string(gkey);
     };
     auto it = db.find(key);
@@ -2288,6 +2421,7 @@ int autotune(MG &mg, const char *db_path, hipStream_t st) {
       for (int v : top_vars)
         for (int g : grids)
           if (grid_ok(v, g)) finals.push_back({v, g});
+      if (lu_possible(mg)) finals.push_back({mg.mixed ? kLu32 : kLu64, gj_batched_grid(mg.npatch_all)});
       double best_ms = 1e300;
       for (auto &fg : finals) {
         mg.gj_variant = fg.first;
@@ -2626,9 +2760,18 @@ fsi_status fsi_mg_export_patches(struct fsi_mg *h, int32_t level, int64_t *ptr, 
       double *B = mg->blk_scratch + L.blk_base;
       launch_fill_f64(B, L.boff_total, 0.0, st);
       launch_extract(L.J.val, L.ext_nslots, L.d_ext_src, L.d_ext_dst, B, st);
-      hip_check(hipMemcpyAsync(blocks, B, sizeof(double) * L.boff_total, hipMemcpyDeviceToHost, st),
+      std::vector<double> host(L.boff_total);
+      hip_check(hipMemcpyAsync(host.data(), B, sizeof(double) * L.boff_total, hipMemcpyDeviceToHost, st),
                 "D2H blocks");
       hip_check(hipStreamSynchronize(st), "export");
+      double *out = blocks;   // without the rows' padding
+      for (int k = 0; k < L.npatch; ++k) {
+        const int64_t m = L.h_ptr[k + 1] - L.h_ptr[k];
+        for (int64_t i = 0; i < m; ++i, out += m) {
+          const double *row = host.data() + L.h_boff[k] + i * block_ld((int)m);
+          std::copy(row, row + m, out);
+        }
+      }
     }
     return FSI_OK;
   })
