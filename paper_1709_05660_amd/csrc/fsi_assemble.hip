@@ -1,14 +1,16 @@
 // Device assembly of the finest residual and its exact Jacobian, and the
 // Newton loop on the device (include/fsi_assembly.h).
 //
-// One workgroup per (element of one colour, range of Jacobian columns).  The
-// element residual's rows are sums over quadrature points of test functions
-// weighted by a few coefficients per point; the workgroup differentiates
-// those coefficients along each of its columns' local dofs (one-direction
-// dual numbers: value and derivative), then contracts them with the
-// test-function tables and adds the element Jacobian's entries into the CSR
-// values at positions found once, when the assembly is created.  Elements of
-// one colour share no node, so every entry is written once per launch.
+// One workgroup per element of one colour.  The element residual's rows are
+// sums over quadrature points of test functions weighted by a few coefficients
+// per point, which depend on the element state through a few sums per point
+// (gradients and values of the fields).  The workgroup differentiates the
+// coefficients along each of these sums (one-direction dual numbers: value and
+// derivative), so the element Jacobian is a product of the test-function
+// table, the points' small tangent matrices and the table again; it is formed
+// on the matrix cores and added into the CSR values at positions found once,
+// when the assembly is created.  Elements of one colour share no node, so
+// every entry is written once per launch.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -18,6 +20,7 @@
 
 #include "../../include/fsi_assembly.h"
 #include "fsi_internal.h"
+#include "fsi_pivot.h"
 
 namespace fsi {
 
@@ -51,139 +54,136 @@ struct Shape {
   static constexpr int NA = DIM == 3 ? 27 : 9, NP = DIM + 1, NL = 2 * DIM * NA + NP, NQ = DIM == 3 ? 27 : 9;
 };
 
-// fields of one state at one quadrature point (as the host builder's Kin)
-template <int DIM, typename V>
-struct KinD {
-  V Gd[DIM][DIM], F[DIM][DIM], Fi[DIM][DIM], det, pq, uq[DIM], dq[DIM], gu[DIM][DIM];
-};
-
 // The sums over the element's nodes at one quadrature point: the reference
 // gradients of displacement and velocity, velocity, displacement and
-// pressure.  They are linear in the element state, and a thread's dual state
-// differs from the element's value by one unit entry (its local dof), so the
-// value sums are taken once per element and point and shared through LDS, and
-// each thread adds its single-term derivative; only the nonlinear part
-// (deformation gradient, determinant, inverse, stresses) runs in duals.
+// pressure.
 template <int DIM>
 struct Sums {
   // per point: Gd[c][j], Gu[c][j], uq[c], dq[c], pq
   static constexpr int GD = 0, GU = DIM * DIM, UQ = 2 * DIM * DIM, DQ = UQ + DIM, PQ = DQ + DIM, NS = PQ + 1;
 };
 
-// sum s of point q for the element state ye
+// sum s of point q for the element state ye; phi[q][a]: the node's reference
+// gradient (two in 2D, then a zero) and its value
 template <int DIM>
-__device__ __forceinline__ double point_sum(const double *sN, const double *sdN, const double *spsi, const double *ye,
-                                            int q, int s) {
+__device__ __forceinline__ double point_sum(const double *phi, const double *spsi, const double *ye, int q, int s) {
   constexpr int NA = Shape<DIM>::NA, NP = Shape<DIM>::NP;
   using S = Sums<DIM>;
-  const double *Nq = sN + q * NA, *dNq = sdN + q * NA * DIM;
   double acc = 0.0;
-  if (s < S::UQ) {
-    const int c = (s % (DIM * DIM)) / DIM, j = s % DIM;
-    const double *yc = ye + (s < S::GU ? c : DIM + c) * NA;
-    for (int a = 0; a < NA; ++a) acc += dNq[a * DIM + j] * yc[a];
-  } else if (s < S::PQ) {
-    const double *yc = ye + (s < S::DQ ? DIM + s - S::UQ : s - S::DQ) * NA;
-    for (int a = 0; a < NA; ++a) acc += Nq[a] * yc[a];
+  if (s < S::PQ) {
+    const int j = s < S::UQ ? s % DIM : 3;
+    const int f = s < S::GU ? s / DIM : s < S::UQ ? DIM + (s - S::GU) / DIM : s < S::DQ ? DIM + s - S::UQ : s - S::DQ;
+    const double *yc = ye + f * NA, *t = phi + q * NA * 4 + j;
+    for (int a = 0; a < NA; ++a) acc += t[a * 4] * yc[a];
   } else {
     for (int j = 0; j < NP; ++j) acc += spsi[q * NP + j] * ye[2 * DIM * NA + j];
   }
   return acc;
 }
 
-// the rest of the kinematics from the gradients (F = I + Gd, its determinant
-// and inverse, and for the fluid the velocity gradient in current coordinates
-// gu = Gu F^{-1}); uq, dq and pq are set by the caller
-template <int DIM, typename V>
-__device__ __forceinline__ void kin_finish(const V (&Gd)[DIM][DIM], const V (&Gu)[DIM][DIM], bool fluid,
-                                           KinD<DIM, V> &k) {
+// What follows from a point's sums without the direction of differentiation,
+// once per point and state: det F, F^{-1} and, for the fluid, the velocity
+// gradient in current coordinates gu = Gu F^{-1}.
+template <int DIM>
+struct Point {
+  static constexpr int DET = 0, FI = 1, GC = FI + DIM * DIM, NP = GC + DIM * DIM;
+};
+template <int DIM>
+__device__ __forceinline__ void point_kinematics(const double *S, bool fluid, double *out) {
+  using SS = Sums<DIM>;
+  using P = Point<DIM>;
+  double F[DIM][DIM], Fi[DIM][DIM], det;
 #pragma unroll
   for (int c = 0; c < DIM; ++c)
 #pragma unroll
-    for (int j = 0; j < DIM; ++j) {
-      k.Gd[c][j] = Gd[c][j];
-      k.F[c][j] = c == j ? Gd[c][j] + 1.0 : Gd[c][j];
-    }
+    for (int j = 0; j < DIM; ++j) F[c][j] = c == j ? S[SS::GD + c * DIM + j] + 1.0 : S[SS::GD + c * DIM + j];
   if constexpr (DIM == 2) {
-    k.det = k.F[0][0] * k.F[1][1] - k.F[0][1] * k.F[1][0];
-    k.Fi[0][0] = k.F[1][1] / k.det;
-    k.Fi[1][1] = k.F[0][0] / k.det;
-    k.Fi[0][1] = -(k.F[0][1] / k.det);
-    k.Fi[1][0] = -(k.F[1][0] / k.det);
+    det = F[0][0] * F[1][1] - F[0][1] * F[1][0];
+    Fi[0][0] = F[1][1] / det;
+    Fi[1][1] = F[0][0] / det;
+    Fi[0][1] = -(F[0][1] / det);
+    Fi[1][0] = -(F[1][0] / det);
   } else {
-    V cof[3][3];
+    double cof[3][3];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const int i1 = (i + 1) % 3, i2 = (i + 2) % 3, j1 = (j + 1) % 3, j2 = (j + 2) % 3;
-        cof[i][j] = k.F[i1][j1] * k.F[i2][j2] - k.F[i1][j2] * k.F[i2][j1];
+        cof[i][j] = F[i1][j1] * F[i2][j2] - F[i1][j2] * F[i2][j1];
       }
-    k.det = k.F[0][0] * cof[0][0] + k.F[0][1] * cof[0][1] + k.F[0][2] * cof[0][2];
+    det = F[0][0] * cof[0][0] + F[0][1] * cof[0][1] + F[0][2] * cof[0][2];
 #pragma unroll
     for (int i = 0; i < 3; ++i)
 #pragma unroll
-      for (int j = 0; j < 3; ++j) k.Fi[i][j] = cof[j][i] / k.det;
+      for (int j = 0; j < 3; ++j) Fi[i][j] = cof[j][i] / det;
   }
-  if (!fluid) return;
+  out[P::DET] = det;
 #pragma unroll
   for (int c = 0; c < DIM; ++c)
 #pragma unroll
     for (int b = 0; b < DIM; ++b) {
-      V s = V{};
+      out[P::FI + c * DIM + b] = Fi[c][b];
+      double g = 0.0;
+      if (fluid)
 #pragma unroll
-      for (int j = 0; j < DIM; ++j) s = s + Gu[c][j] * k.Fi[j][b];
-      k.gu[c][b] = s;
+        for (int j = 0; j < DIM; ++j) g += S[SS::GU + c * DIM + j] * Fi[j][b];
+      out[P::GC + c * DIM + b] = g;
     }
 }
 
-// kinematics of the state at t_n from its shared sums
+// The fields of a point's state, read from its sums and kinematics.
 template <int DIM>
-__device__ __forceinline__ void kin_value(const double *S, bool fluid, KinD<DIM, double> &k) {
+struct Fields {
+  const double *S, *K;
   using SS = Sums<DIM>;
-  double Gd[DIM][DIM], Gu[DIM][DIM];
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
+  using P = Point<DIM>;
+  __device__ __forceinline__ double det() const { return K[P::DET]; }
+  __device__ __forceinline__ double Gd(int c, int j) const { return S[SS::GD + c * DIM + j]; }
+  __device__ __forceinline__ double F(int c, int j) const { return c == j ? Gd(c, j) + 1.0 : Gd(c, j); }
+  __device__ __forceinline__ double Fi(int c, int j) const { return K[P::FI + c * DIM + j]; }
+  __device__ __forceinline__ double gu(int c, int j) const { return K[P::GC + c * DIM + j]; }
+  __device__ __forceinline__ double u(int c) const { return S[SS::UQ + c]; }
+  __device__ __forceinline__ double d(int c) const { return S[SS::DQ + c]; }
+  __device__ __forceinline__ double p() const { return S[SS::PQ]; }
+};
+// The same differentiated along sum s.  Along the entry (m, n) of the
+// displacement gradient F changes by a rank-one matrix: d det = det Fi[n][m],
+// d Fi[i][j] = -Fi[i][m] Fi[n][j], d gu[i][j] = -gu[i][m] Fi[n][j]; along that
+// of the velocity gradient d gu[m][j] = Fi[n][j].
+template <int DIM>
+struct DualFields {
+  Fields<DIM> f;
+  int s, m, n;
+  bool gd, gv;
+  using SS = Sums<DIM>;
+  using P = Point<DIM>;
+  double row[DIM], fi[DIM], gc[DIM], ddet;   // row n of F^{-1} and its factors
+  __device__ __forceinline__ DualFields(const double *S, const double *K, int s_) : f{S, K}, s(s_) {
+    gd = s < SS::GU;
+    gv = !gd && s < SS::UQ;
+    m = gd || gv ? (s % (DIM * DIM)) / DIM : 0;
+    n = gd || gv ? s % DIM : 0;
+    ddet = gd ? f.det() * f.Fi(n, m) : 0.0;
 #pragma unroll
     for (int j = 0; j < DIM; ++j) {
-      Gd[c][j] = S[SS::GD + c * DIM + j];
-      Gu[c][j] = S[SS::GU + c * DIM + j];
+      row[j] = f.Fi(n, j);
+      fi[j] = gd ? -f.Fi(j, m) : 0.0;
+      gc[j] = gd ? -f.gu(j, m) : gv && j == m ? 1.0 : 0.0;
     }
-    k.uq[c] = S[SS::UQ + c];
-    k.dq[c] = S[SS::DQ + c];
   }
-  k.pq = S[SS::PQ];
-  kin_finish<DIM>(Gd, Gu, fluid, k);
-}
-
-// kinematics of the current state differentiated along local dof jd: the
-// shared value sums plus the one term that dof contributes to each
-template <int DIM>
-__device__ __forceinline__ void kin_dual(const double *S, const double *Nq, const double *dNq, const double *ps,
-                                         int jd, bool fluid, KinD<DIM, D1> &k) {
-  constexpr int NA = Shape<DIM>::NA;
-  using SS = Sums<DIM>;
-  const bool isd = jd < DIM * NA, isv = !isd && jd < 2 * DIM * NA, isp = jd >= 2 * DIM * NA;
-  const int tc = isd ? jd / NA : (isv ? (jd - DIM * NA) / NA : -1);
-  const int ta = isp ? 0 : jd % NA;
-  const double nq = Nq[ta], pp = isp ? ps[jd - 2 * DIM * NA] : 0.0;
-  double dn[DIM];
-#pragma unroll
-  for (int j = 0; j < DIM; ++j) dn[j] = dNq[ta * DIM + j];
-  D1 Gd[DIM][DIM], Gu[DIM][DIM];
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-#pragma unroll
-    for (int j = 0; j < DIM; ++j) {
-      Gd[c][j] = {S[SS::GD + c * DIM + j], isd && c == tc ? dn[j] : 0.0};
-      Gu[c][j] = {S[SS::GU + c * DIM + j], isv && c == tc ? dn[j] : 0.0};
-    }
-    k.uq[c] = {S[SS::UQ + c], isv && c == tc ? nq : 0.0};
-    k.dq[c] = {S[SS::DQ + c], isd && c == tc ? nq : 0.0};
-  }
-  k.pq = {S[SS::PQ], pp};
-  kin_finish<DIM>(Gd, Gu, fluid, k);
-}
+  __device__ __forceinline__ D1 unit(double v, int i) const { return {v, s == i ? 1.0 : 0.0}; }
+  __device__ __forceinline__ D1 det() const { return {f.det(), ddet}; }
+  __device__ __forceinline__ D1 Gd(int c, int j) const { return unit(f.Gd(c, j), SS::GD + c * DIM + j); }
+  __device__ __forceinline__ D1 F(int c, int j) const { return unit(f.F(c, j), SS::GD + c * DIM + j); }
+  // (row c given apart: a runtime index into registers would go to memory)
+  __device__ __forceinline__ D1 Fi(int c, int j) const { return {f.Fi(c, j), fi[c] * row[j]}; }
+  __device__ __forceinline__ D1 gu(int c, int j) const { return {f.gu(c, j), gc[c] * row[j]}; }
+  __device__ __forceinline__ D1 gu_row(int c, double gcc, int j) const { return {f.gu(c, j), gcc * row[j]}; }
+  __device__ __forceinline__ D1 u(int c) const { return unit(f.u(c), SS::UQ + c); }
+  __device__ __forceinline__ D1 d(int c) const { return unit(f.d(c), SS::DQ + c); }
+  __device__ __forceinline__ D1 p() const { return unit(f.p(), SS::PQ); }
+};
 
 // structural coupling of local row lr with local column lc (the builder's rule)
 __device__ __forceinline__ bool coupled_d(int dim, int na, bool solid, bool transient, int lr, int lc) {
@@ -206,259 +206,378 @@ __device__ __forceinline__ bool coupled_d(int dim, int na, bool solid, bool tran
 // weighted by a few per-point coefficients: for the momentum rows of
 // component c the coefficients of N_a and of dN_a/dX_j, likewise for the mesh
 // motion (fluid) or kinematic (solid) rows, and one coefficient for the
-// pressure rows.  Their derivatives along a local dof follow from the
-// point's dual kinematics; the element Jacobian is then the contraction of
-// the test-function tables with these derivatives.
+// pressure rows.  Order: the coefficients of the gradient, then that of N_a
+// (four in 2D too, one of them zero).
 template <int DIM>
 struct Terms {
-  static constexpr int K = 1 + DIM;   // N_a, dN_a/dX_0 .. dN_a/dX_{DIM-1}
-  static constexpr int MOM = 0, MESH = DIM * K, PR = 2 * DIM * K, NK = PR + 1;
+  static constexpr int MOM = 0, MESH = DIM * 4, PR = 2 * DIM * 4, NK = PR + 1;
+  // with a tangent of their own: the momentum and pressure coefficients (those
+  // of the mesh motion and of the kinematics are linear in one sum)
+  static constexpr int TPR = DIM * 4, NT = TPR + 1;
+};
+// groups of columns that share a field component (displacement, velocity,
+// pressure): a column of node b sums its group's tangents along the gradient
+// and the value, weighted by the node's table entries
+template <int DIM>
+struct Groups {
+  static constexpr int NG = 2 * DIM + 1;
+  static __device__ __forceinline__ int group(int s) {
+    using S = Sums<DIM>;
+    return s < S::GU ? s / DIM
+           : s < S::UQ ? DIM + (s - S::GU) / DIM
+           : s < S::DQ ? DIM + s - S::UQ
+           : s < S::PQ ? s - S::DQ
+                       : 2 * DIM;
+  }
+  static __device__ __forceinline__ int slot(int s) {
+    using S = Sums<DIM>;
+    return s < S::UQ ? s % DIM : s < S::PQ ? 3 : 0;
+  }
 };
 
-// The coefficients of one point for one column of the element: their
-// derivatives along local dof jd, or with value set their values (the
-// residual), the formulas of the host builder (steady, or one Crank-Nicolson
-// step when sums0, the sums of the state at t_n, is given).
+// The coefficients of one point for the rows of component c (the pressure
+// rows with c = 0): their derivatives along sum s (tan, stride 4 between
+// coefficients) and, for vals not null, their values (the residual), the
+// formulas of the host builder (steady, or one Crank-Nicolson step when cn,
+// f0 then the state at t_n).
 template <int DIM>
-__device__ __forceinline__ void point_terms(const AsmView &v, bool solid, const double *sums, const double *sums0,
-                                            const double *Nq, const double *dNq, const double *ps, double w, int jd,
-                                            bool value, double *out) {
+__device__ __forceinline__ void point_terms(const AsmView &v, bool solid, bool cn, const DualFields<DIM> &k1,
+                                            const Fields<DIM> &k0, double w, int c, double *tan, double *vals) {
   using T = Terms<DIM>;
-  const bool cn = sums0 != nullptr;
   const double dt = v.dt, rho = v.rho, mu = v.mu;
-  const double k_ale = 1.0 / v.vol;
-  KinD<DIM, D1> k1;
-  kin_dual<DIM>(sums, Nq, dNq, ps, jd, !solid, k1);
-  // per-point quantities of the rows: momentum (S, Tm), mesh motion /
-  // kinematics (A), continuity / incompressibility (Pr)
-  D1 S[DIM], Tm[DIM][DIM], A[DIM], Pr;
-  double Tm0[DIM][DIM];
-  bool with_S = true;
+  auto put = [&](int j, D1 x) {   // momentum coefficient j
+    tan[(c * 4 + j) * 4] = x.g;
+    if (vals) vals[T::MOM + c * 4 + j] = x.v;
+  };
+  auto put_mesh = [&](int j, double x) {
+    if (vals) vals[T::MESH + c * 4 + j] = x;
+  };
+  D1 S = dc(0.0), Pr;
   if (!solid) {
-    D1 sig1[DIM][DIM];
-    for (int c = 0; c < DIM; ++c)
-      for (int b = 0; b < DIM; ++b) {
-        sig1[c][b] = mu * (k1.gu[c][b] + k1.gu[b][c]);
-        if (b == c) sig1[c][b] = sig1[c][b] - k1.pq;
-      }
-    const D1 wJ1 = w * k1.det;
-    if (!cn) {
-      for (int c = 0; c < DIM; ++c) {
-        D1 t = dc(0.0);
-        for (int b = 0; b < DIM; ++b) t = t + k1.gu[c][b] * k1.uq[b];
-        S[c] = rho * (wJ1 * t);
-        for (int j = 0; j < DIM; ++j) {
-          D1 t2 = dc(0.0);
-          for (int b = 0; b < DIM; ++b) t2 = t2 + sig1[c][b] * k1.Fi[j][b];
-          Tm[c][j] = wJ1 * t2;
-          Tm0[c][j] = 0.0;
-        }
-      }
-    } else {
-      KinD<DIM, double> k0;
-      kin_value<DIM>(sums0, true, k0);
-      double sig0[DIM][DIM];
-      for (int c = 0; c < DIM; ++c)
-        for (int b = 0; b < DIM; ++b) {
-          sig0[c][b] = mu * (k0.gu[c][b] + k0.gu[b][c]);
-          if (b == c) sig0[c][b] -= k0.pq;
-        }
-      const double wJ0 = w * k0.det;
-      D1 wq[DIM], Gw[DIM][DIM];
-      for (int c = 0; c < DIM; ++c) {
-        wq[c] = (1.0 / dt) * k1.dq[c] + (-k0.dq[c] / dt);
-        for (int j = 0; j < DIM; ++j) Gw[c][j] = (1.0 / dt) * k1.Gd[c][j] + (-k0.Gd[c][j] / dt);
-      }
-      D1 divw1 = dc(0.0), divw0 = dc(0.0);
-      for (int c = 0; c < DIM; ++c)
-        for (int j = 0; j < DIM; ++j) {
-          divw1 = divw1 + Gw[c][j] * k1.Fi[j][c];
-          divw0 = divw0 + k0.Fi[j][c] * Gw[c][j];
-        }
-      for (int c = 0; c < DIM; ++c) {
-        D1 t1 = -(divw1 * k1.uq[c]);
-        for (int b = 0; b < DIM; ++b) t1 = t1 + k1.gu[c][b] * k1.uq[b] - k1.gu[c][b] * wq[b];
-        t1 = (0.5 * rho) * t1 + (rho / dt) * k1.uq[c];
-        D1 t2 = (-k0.uq[c]) * divw0;
-        for (int b = 0; b < DIM; ++b) t2 = t2 + k0.gu[c][b] * k0.uq[b] + (-k0.gu[c][b]) * wq[b];
-        t2 = (0.5 * rho) * t2 + (-(rho / dt) * k0.uq[c]);
-        S[c] = wJ1 * t1 + wJ0 * t2;
-        for (int j = 0; j < DIM; ++j) {
-          D1 s1 = dc(0.0);
-          double c0 = 0.0;
-          for (int b = 0; b < DIM; ++b) {
-            s1 = s1 + sig1[c][b] * k1.Fi[j][b];
-            c0 += sig0[c][b] * k0.Fi[j][b];
-          }
-          Tm[c][j] = 0.5 * (wJ1 * s1);
-          Tm0[c][j] = 0.5 * wJ0 * c0;
-        }
-      }
+    const D1 wJ1 = w * k1.det();
+    double gcc = k1.gc[0];
+    D1 sig[DIM], guc[DIM];
+#pragma unroll
+    for (int b = 1; b < DIM; ++b) gcc = c == b ? k1.gc[b] : gcc;
+#pragma unroll
+    for (int b = 0; b < DIM; ++b) {
+      guc[b] = k1.gu_row(c, gcc, b);
+      // column c of gu: row b times entry c of the direction's row
+      double rc = k1.row[0];
+#pragma unroll
+      for (int j = 1; j < DIM; ++j) rc = c == j ? k1.row[j] : rc;
+      sig[b] = mu * (guc[b] + D1{k1.f.gu(b, c), k1.gc[b] * rc});
+      if (b == c) sig[b] = sig[b] - k1.p();
     }
-    for (int c = 0; c < DIM; ++c) A[c] = dc(0.0);   // the mesh motion uses Gd directly
-    D1 div = dc(0.0);
-    for (int c = 0; c < DIM; ++c) div = div + k1.gu[c][c];
-    Pr = wJ1 * div;
+    if (!cn) {
+      D1 t = dc(0.0);
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) t = t + guc[b] * k1.u(b);
+      S = rho * (wJ1 * t);
+    } else {
+      const double wJ0 = w * k0.det();
+      D1 divw1 = dc(0.0), divw0 = dc(0.0);
+#pragma unroll
+      for (int i = 0; i < DIM; ++i)
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) {
+          const D1 Gw = (1.0 / dt) * k1.Gd(i, j) + (-k0.Gd(i, j) / dt);
+          divw1 = divw1 + Gw * k1.Fi(j, i);
+          divw0 = divw0 + k0.Fi(j, i) * Gw;
+        }
+      D1 t1 = -(divw1 * k1.u(c));
+      D1 t2 = (-k0.u(c)) * divw0;
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) {
+        const D1 wq = (1.0 / dt) * k1.d(b) + (-k0.d(b) / dt);
+        t1 = t1 + guc[b] * k1.u(b) - guc[b] * wq;
+        t2 = t2 + k0.gu(c, b) * k0.u(b) + (-k0.gu(c, b)) * wq;
+      }
+      t1 = (0.5 * rho) * t1 + (rho / dt) * k1.u(c);
+      t2 = (0.5 * rho) * t2 + (-(rho / dt) * k0.u(c));
+      S = wJ1 * t1 + wJ0 * t2;
+    }
+    const double k_ale = 1.0 / v.vol;
+#pragma unroll
+    for (int j = 0; j < DIM; ++j) {
+      D1 t = dc(0.0);
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) t = t + sig[b] * k1.Fi(j, b);
+      D1 Tm = wJ1 * t;
+      if (cn) {
+        double t0 = 0.0;
+        const double wJ0 = w * k0.det();
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) {
+          double s0 = mu * (k0.gu(c, b) + k0.gu(b, c));
+          if (b == c) s0 -= k0.p();
+          t0 += s0 * k0.Fi(j, b);
+        }
+        Tm = 0.5 * Tm + 0.5 * wJ0 * t0;
+      }
+      put(j, Tm);
+      put_mesh(j, (w * k_ale) * k1.f.Gd(c, j));
+    }
+    put(3, S);
+    put_mesh(3, 0.0);
+    if (c == 0) {
+      D1 div = dc(0.0);
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) div = div + k1.gu(b, b);
+      Pr = wJ1 * div;
+    }
   } else {
     // Piola stress J sigma F^{-T}, sigma = -p I + mu_s F F^T
-    D1 sig[DIM][DIM];
-    for (int c = 0; c < DIM; ++c)
-      for (int b = 0; b < DIM; ++b) {
-        D1 s = dc(0.0);
-        for (int j = 0; j < DIM; ++j) s = s + k1.F[c][j] * k1.F[b][j];
-        sig[c][b] = v.mu_s * s;
-        if (b == c) sig[c][b] = sig[c][b] - k1.pq;
+    D1 sig[DIM];
+    double sg0[DIM];
+#pragma unroll
+    for (int b = 0; b < DIM; ++b) {
+      D1 t = dc(0.0);
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) t = t + k1.F(c, j) * k1.F(b, j);
+      sig[b] = v.mu_s * t;
+      if (b == c) sig[b] = sig[b] - k1.p();
+      if (cn) {
+        double t0 = 0.0;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) t0 += k0.F(c, j) * k0.F(b, j);
+        sg0[b] = v.mu_s * t0 - (b == c ? k0.p() : 0.0);
       }
-    for (int c = 0; c < DIM; ++c)
-      for (int b = 0; b < DIM; ++b) {
-        D1 s = dc(0.0);
-        for (int j = 0; j < DIM; ++j) s = s + sig[c][j] * k1.Fi[b][j];
-        Tm[c][b] = k1.det * s;
-        Tm0[c][b] = 0.0;
+    }
+    const D1 det = k1.det();
+#pragma unroll
+    for (int b = 0; b < DIM; ++b) {
+      D1 t = dc(0.0);
+#pragma unroll
+      for (int j = 0; j < DIM; ++j) t = t + sig[j] * k1.Fi(b, j);
+      D1 Tm = det * t;
+      if (cn) {
+        double t0 = 0.0;
+#pragma unroll
+        for (int j = 0; j < DIM; ++j) t0 += sg0[j] * k0.Fi(b, j);
+        Tm = 0.5 * (Tm + k0.det() * t0);
       }
-    with_S = cn;
+      put(b, w * Tm);
+      put_mesh(b, 0.0);
+    }
+    double A = k1.f.u(c);
     if (cn) {
-      KinD<DIM, double> k0;
-      kin_value<DIM>(sums0, false, k0);
-      double sg0[DIM][DIM];
-      for (int c = 0; c < DIM; ++c)
-        for (int b = 0; b < DIM; ++b) {
-          double s = 0.0;
-          for (int j = 0; j < DIM; ++j) s += k0.F[c][j] * k0.F[b][j];
-          sg0[c][b] = v.mu_s * s - (b == c ? k0.pq : 0.0);
-        }
-      for (int c = 0; c < DIM; ++c) {
-        for (int b = 0; b < DIM; ++b) {
-          double s = 0.0;
-          for (int j = 0; j < DIM; ++j) s += sg0[c][j] * k0.Fi[b][j];
-          Tm0[c][b] = k0.det * s;
-        }
-        S[c] = (v.rho_s / dt) * (k1.det * k1.uq[c] + (-k0.det * k0.uq[c]));
-        A[c] = (-1.0 / dt) * k1.dq[c] + 0.5 * k1.uq[c] + (k0.dq[c] / dt + 0.5 * k0.uq[c]);
-      }
-    } else {
-      for (int c = 0; c < DIM; ++c) {
-        S[c] = dc(0.0);
-        A[c] = k1.uq[c];
-      }
+      S = (v.rho_s / dt) * (det * k1.u(c) + (-k0.det() * k0.u(c)));
+      A = (-1.0 / dt) * k1.f.d(c) + 0.5 * k1.f.u(c) + (k0.d(c) / dt + 0.5 * k0.u(c));
     }
-    Pr = k1.det + (-1.0);
+    put(3, w * S);
+    put_mesh(3, w * A);
+    Pr = w * (det + (-1.0));
   }
-  const double half = (solid && cn) ? 0.5 : 1.0;
-  auto put = [&](int i, D1 x) { out[i] = value ? x.v : x.g; };
-#pragma unroll
-  for (int c = 0; c < DIM; ++c) {
-    if (!solid) {
-      put(T::MOM + c * T::K, S[c]);
-      put(T::MESH + c * T::K, dc(0.0));
-#pragma unroll
-      for (int j = 0; j < DIM; ++j) {
-        put(T::MOM + c * T::K + 1 + j, Tm[c][j] + Tm0[c][j]);
-        put(T::MESH + c * T::K + 1 + j, (w * k_ale) * k1.Gd[c][j]);
-      }
-    } else {
-      put(T::MOM + c * T::K, with_S ? w * S[c] : dc(0.0));
-      put(T::MESH + c * T::K, w * A[c]);
-#pragma unroll
-      for (int j = 0; j < DIM; ++j) {
-        put(T::MOM + c * T::K + 1 + j, (half * w) * (Tm[c][j] + Tm0[c][j]));
-        put(T::MESH + c * T::K + 1 + j, dc(0.0));
-      }
-    }
+  if (DIM == 2) {
+    put(2, dc(0.0));
+    put_mesh(2, 0.0);
   }
-  put(T::PR, solid ? w * Pr : Pr);
+  if (c == 0) {
+    tan[T::TPR * 4] = Pr.g;
+    if (vals) vals[T::PR] = Pr.v;
+  }
 }
 
-// Assembly of one element, columns [c0, c0 + DC) of its Jacobian, column NL
-// standing for the residual.  Phase 1: the point sums of the element state
-// (and of the state at t_n).  Phase 2: the coefficients of every (column,
-// point) pair into LDS.  Phase 3: each thread contracts one row's test
-// function with CPT columns' coefficients and adds the results at the
-// positions the map gives (-1: not stored).  Elements of one colour share no
-// node, so no two threads of a launch add to one entry.
-template <int DIM, int DC, int CPT, int NT>
-__global__ __launch_bounds__(NT) void k_assemble(AsmView v, const double *__restrict__ y, double *__restrict__ r,
-                                                 double *__restrict__ jval, const int *__restrict__ map, int cbase,
-                                                 int nsplit) {
+// Assembly of one element.  Phase 1: the point sums of the element state (and
+// of the state at t_n) and what follows from them.  Phase 2: the tangents of
+// every (point, sum, component) and the points' coefficients, into LDS.  Phase
+// 3, the element Jacobian: each wave takes the columns of 16 nodes of one
+// field component and the rows of one component at a time.  One point is one
+// step of the 16x16x4 product: A holds the row node's table entries, B the
+// tangents times the column node's, formed in registers (so the tangents are
+// read from LDS, a few addresses per wave, and never multiplied out there).
+// The entries' positions and present sums are loaded before the products.
+// Rows or columns past the element's nodes repeat its last node and are
+// dropped.
+// A launch is a colour (256 of 2,048 elements in 3D, 1,024 of 4,096 in 2D), so
+// one workgroup's latency bounds it in 3D: loads, sums, tangents (16 us with 8
+// waves), then products whose 2,500 steps take 17 us of the FP64 matrix cores,
+// and the scattered additions.  With 16 waves a launch takes 48 us (8 waves:
+// 55, 12: 51) against 443 us for dual numbers along all 166 local dofs and a
+// contraction on the vector units; in 2D 18 us against 39.  An assembly:
+// 32x8x8 3,577 -> 408 us, 128x32 time step 158 -> 86 us.
+template <int DIM, int NT, int WPS>
+__global__ __launch_bounds__(NT, WPS) void k_assemble(AsmView v, const double *__restrict__ y, double *__restrict__ r,
+                                                 double *__restrict__ jval, const int *__restrict__ map, int cbase) {
   constexpr int NA = Shape<DIM>::NA, NP = Shape<DIM>::NP, NL = Shape<DIM>::NL, NQ = Shape<DIM>::NQ;
-  constexpr int NS = Sums<DIM>::NS, NK = Terms<DIM>::NK, K = Terms<DIM>::K;
-  static_assert(DC % CPT == 0, "columns per thread must divide the columns per block");
+  using S = Sums<DIM>;
+  using T = Terms<DIM>;
+  using G = Groups<DIM>;
+  typedef Mfma16<double> MM;
+  constexpr int NS = S::NS, NTL = (NA + 15) / 16, NG = G::NG;   // node tiles
   __shared__ double ye[NL], ye0[NL];
-  __shared__ int tg[NL];
-  __shared__ double sN[NQ * NA], sdN[NQ * NA * DIM], spsi[NQ * NP], sw[NQ];
-  __shared__ double sums[NQ * NS], sums0[NQ * NS];
-  __shared__ double terms[DC * NQ * NK];
-  const int e = v.color_elems[cbase + blockIdx.x / nsplit];
-  const int c0 = (blockIdx.x % nsplit) * DC;
-  const bool solid = v.solid[e] != 0;
+  __shared__ __align__(32) double phi[NQ * NA * 4];
+  __shared__ double spsi[NQ * NP], sw[NQ];
+  constexpr int NKIN = Point<DIM>::NP;
+  __shared__ double sums[NQ * NS], sums0[NQ * NS], vals[NQ * T::NK], kin[NQ * NKIN], kin0[NQ * NKIN];
+  __shared__ __align__(32) double tan[NQ * NG * T::NT * 4];
+  const int e = v.color_elems[cbase + blockIdx.x];
+  const bool solid = v.solid[e] != 0, transient = v.transient != 0;
   for (int i = threadIdx.x; i < NL; i += NT) {
     const int g = v.l2g[(int64_t)e * NL + i];
-    tg[i] = v.tgt[(int64_t)e * NL + i];
     ye[i] = y[g];
-    ye0[i] = v.transient ? v.yprev[g] : 0.0;
+    ye0[i] = transient ? v.yprev[g] : 0.0;
   }
-  for (int i = threadIdx.x; i < NQ * NA; i += NT) sN[i] = v.N[i];
-  for (int i = threadIdx.x; i < NQ * NA * DIM; i += NT) sdN[i] = v.dN[i];
+  for (int i = threadIdx.x; i < NQ * NA; i += NT) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) phi[i * 4 + j] = j < DIM ? v.dN[i * DIM + j] : 0.0;
+    phi[i * 4 + 3] = v.N[i];
+  }
   for (int i = threadIdx.x; i < NQ * NP; i += NT) spsi[i] = v.psi[i];
   for (int i = threadIdx.x; i < NQ; i += NT) sw[i] = v.w[i];
+  if (DIM == 2)   // the third gradient slots stay zero
+    for (int i = threadIdx.x; i < NQ * NG * T::NT * 4; i += NT) tan[i] = 0.0;
   __syncthreads();
   for (int i = threadIdx.x; i < NQ * NS; i += NT) {
-    sums[i] = point_sum<DIM>(sN, sdN, spsi, ye, i / NS, i % NS);
-    if (v.transient) sums0[i] = point_sum<DIM>(sN, sdN, spsi, ye0, i / NS, i % NS);
+    sums[i] = point_sum<DIM>(phi, spsi, ye, i / NS, i % NS);
+    if (transient) sums0[i] = point_sum<DIM>(phi, spsi, ye0, i / NS, i % NS);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < DC * NQ; i += NT) {
-    const int cl = i / NQ, q = i % NQ, col = c0 + cl;
-    if (col > NL) continue;
-    point_terms<DIM>(v, solid, sums + q * NS, v.transient ? sums0 + q * NS : nullptr, sN + q * NA,
-                     sdN + q * NA * DIM, spsi + q * NP, sw[q], col == NL ? 0 : col, col == NL, terms + i * NK);
+  for (int i = threadIdx.x; i < (transient ? 2 : 1) * NQ; i += NT) {
+    const int q = i % NQ;
+    point_kinematics<DIM>((i < NQ ? sums : sums0) + q * NS, !solid, (i < NQ ? kin : kin0) + q * NKIN);
   }
   __syncthreads();
-  for (int it = threadIdx.x; it < NL * (DC / CPT); it += NT) {
-    const int lr = it % NL, cg = (it / NL) * CPT;
-    // the row's test function: offset of its coefficients, node, and how many
-    int off, a, nk;
+  for (int i = threadIdx.x; i < NQ * NS * DIM; i += NT) {
+    const int q = i % NQ, c = (i / NQ) % DIM, s = i / (NQ * DIM);
+    const DualFields<DIM> k1(sums + q * NS, kin + q * NKIN, s);
+    const Fields<DIM> k0{sums0 + q * NS, kin0 + q * NKIN};
+    point_terms<DIM>(v, solid, transient, k1, k0, sw[q], c, tan + (q * NG + G::group(s)) * T::NT * 4 + G::slot(s),
+                     s == 0 ? vals + q * T::NK : nullptr);
+  }
+  __syncthreads();
+  for (int lr = threadIdx.x; lr < NL; lr += NT) {
+    const int tr = v.tgt[(int64_t)e * NL + lr];
+    if (tr < 0) continue;
+    double acc = 0.0;
     if (lr < 2 * DIM * NA) {
-      const int blk = lr / (DIM * NA), c = (lr % (DIM * NA)) / NA;
-      off = (blk == 0 ? Terms<DIM>::MOM : Terms<DIM>::MESH) + c * K;
-      a = lr % NA;
-      nk = K;
+      const double *t = phi + (lr % NA) * 4, *c = vals + (lr / NA) * 4;
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc += t[q * NA * 4 + j] * c[q * T::NK + j];
     } else {
-      off = Terms<DIM>::PR;
-      a = lr - 2 * DIM * NA;
-      nk = 1;
+      for (int q = 0; q < NQ; ++q) acc += spsi[q * NP + lr - 2 * DIM * NA] * vals[q * T::NK + T::PR];
     }
-    double acc[CPT];
+    r[tr] += acc;
+  }
+  const int lane = threadIdx.x & 63, jl = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int *emap = map + (int64_t)e * NL * NL;
+  // a tile's entries: their positions (rows lr0 + 16 rt + .., nr rows in all; column lc or -1) and what is there
+  struct Entries {
+    int pos[4];
+    double old[4];
+  };
+  auto positions = [&](int lr0, int rt, int nr, int lc, Entries &t) {
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) acc[k] = 0.0;
-    for (int q = 0; q < NQ; ++q) {
-      const double *tq = terms + (cg * NQ + q) * NK + off;
-      if (nk == 1) {
-        const double f = spsi[q * NP + a];
+    for (int k = 0; k < 4; ++k) {
+      const int a = rt * 16 + MM::row(k, kq);
+      t.pos[k] = a < nr && lc >= 0 ? emap[(lr0 + a) * NL + lc] : -1;
+    }
+  };
+  auto load = [&](Entries &t) {
 #pragma unroll
-        for (int k = 0; k < CPT; ++k) acc[k] += f * tq[k * NQ * NK];
+    for (int k = 0; k < 4; ++k) t.old[k] = jval[max(t.pos[k], 0)];
+  };
+  auto add = [&](const Entries &t, const dx4 &c, double f) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (t.pos[k] >= 0) jval[t.pos[k]] = t.old[k] + f * c[k];
+  };
+  const dx4 zero = {0, 0, 0, 0};
+  // Items: 16 nodes' columns of a displacement or velocity component for the
+  // rows of one momentum component or of the pressure, the pressure columns,
+  // the mesh motion or kinematic rows of every component.
+  constexpr int NC = 2 * DIM * NTL, NV = NC * DIM, NI = NV + DIM + DIM * NTL + NC;
+  for (int it = wave; it < NI; it += NT / 64) {
+    if (it < NV + DIM) {
+      const bool prc = it >= NV;   // the pressure columns
+      const int c = it % DIM, g = prc ? 2 * DIM : it / DIM / NTL, ct = prc ? 0 : it / DIM % NTL;
+      if (solid && !prc && g >= DIM && !(transient && g - DIM == c)) continue;
+      const int b = ct * 16 + jl, nb = prc ? NP : NA, bc = min(b, nb - 1);
+      const int lc = b < nb ? (prc ? 2 * DIM * NA : g * NA) + b : -1;
+      dx4 acc[NTL];
+      Entries en[NTL];
+#pragma unroll
+      for (int rt = 0; rt < NTL; ++rt) {
+        acc[rt] = zero;
+        positions(c * NA, rt, NA, lc, en[rt]);
+      }
+#pragma unroll
+      for (int rt = 0; rt < NTL; ++rt) load(en[rt]);
+      const double *t = tan + (g * T::NT + c * 4 + kq) * 4;
+      if (prc) {
+        for (int q = 0; q < NQ; ++q) {
+          const double x = t[q * NG * T::NT * 4] * spsi[q * NP + bc];
+#pragma unroll
+          for (int rt = 0; rt < NTL; ++rt)
+            acc[rt] = MM::mma(phi[(q * NA + min(rt * 16 + jl, NA - 1)) * 4 + kq], x, acc[rt]);
+        }
       } else {
-        double f[K];
-        f[0] = sN[q * NA + a];
+        const double *pb = phi + bc * 4;
+#pragma unroll 3
+        for (int q = 0; q < NQ; ++q) {
+          const double *tq = t + q * NG * T::NT * 4, *pq = pb + q * NA * 4;
+          const double x = fma(tq[3], pq[3], fma(tq[2], pq[2], fma(tq[1], pq[1], tq[0] * pq[0])));
 #pragma unroll
-        for (int j = 0; j < DIM; ++j) f[1 + j] = sdN[(q * NA + a) * DIM + j];
-#pragma unroll
-        for (int k = 0; k < CPT; ++k)
-#pragma unroll
-          for (int j = 0; j < K; ++j) acc[k] += f[j] * tq[k * NQ * NK + j];
+          for (int rt = 0; rt < NTL; ++rt)
+            acc[rt] = MM::mma(phi[(q * NA + min(rt * 16 + jl, NA - 1)) * 4 + kq], x, acc[rt]);
+        }
       }
-    }
-    const int tr = tg[lr];
-    const int *mrow = map + ((int64_t)e * NL + lr) * NL;
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-      const int col = c0 + cg + k;
-      if (col < NL) {
-        const int pos = mrow[col];
-        if (pos >= 0) jval[pos] += acc[k];
-      } else if (col == NL && tr >= 0) {
-        r[tr] += acc[k];
+      for (int rt = 0; rt < NTL; ++rt) add(en[rt], acc[rt], 1.0);
+    } else if (it < NV + DIM + DIM * NTL) {
+      // fluid: w / vol grad N_a . grad N_b in the displacement; solid: w N_a
+      // N_b in the velocity and, in a time step, the displacement
+      const int c = (it - NV - DIM) / NTL, ct = (it - NV - DIM) % NTL;
+      const int b = ct * 16 + jl, bc = min(b, NA - 1);
+      dx4 acc[NTL];
+      Entries ed[NTL], eu[NTL];
+#pragma unroll
+      for (int rt = 0; rt < NTL; ++rt) {
+        acc[rt] = zero;
+        positions((DIM + c) * NA, rt, NA, b < NA && (!solid || transient) ? c * NA + b : -1, ed[rt]);
+        positions((DIM + c) * NA, rt, NA, b < NA && solid ? (DIM + c) * NA + b : -1, eu[rt]);
       }
+#pragma unroll
+      for (int rt = 0; rt < NTL; ++rt) {
+        load(ed[rt]);
+        load(eu[rt]);
+      }
+      const bool on = solid ? kq == 3 : kq < DIM;
+      const double k_ale = 1.0 / v.vol;
+#pragma unroll 3
+      for (int q = 0; q < NQ; ++q) {
+        const double wq = solid ? sw[q] : sw[q] * k_ale;
+        const double x = on ? wq * phi[(q * NA + bc) * 4 + kq] : 0.0;
+#pragma unroll
+        for (int rt = 0; rt < NTL; ++rt)
+          acc[rt] = MM::mma(phi[(q * NA + min(rt * 16 + jl, NA - 1)) * 4 + kq], x, acc[rt]);
+      }
+#pragma unroll
+      for (int rt = 0; rt < NTL; ++rt) {
+        add(ed[rt], acc[rt], solid ? -1.0 / v.dt : 1.0);
+        add(eu[rt], acc[rt], transient ? 0.5 : 1.0);
+      }
+    } else {
+      // the pressure rows, four points a step
+      const int g = (it - NV - DIM - DIM * NTL) / NTL, ct = (it - NV - DIM - DIM * NTL) % NTL;
+      if (solid && g >= DIM) continue;
+      const int b = ct * 16 + jl, bc = min(b, NA - 1);
+      Entries en;
+      positions(2 * DIM * NA, 0, NP, b < NA ? g * NA + b : -1, en);
+      load(en);
+      dx4 acc = zero;
+#pragma unroll
+      for (int q0 = 0; q0 < NQ; q0 += 4) {
+        const bool ok = q0 + kq < NQ;
+        const int q = min(q0 + kq, NQ - 1);
+        const double *t = tan + ((q * NG + g) * T::NT + T::TPR) * 4, *pb = phi + (q * NA + bc) * 4;
+        const double x = fma(t[3], pb[3], fma(t[2], pb[2], fma(t[1], pb[1], t[0] * pb[0])));
+        acc = MM::mma(ok ? spsi[q * NP + min(jl, NP - 1)] : 0.0, ok ? x : 0.0, acc);
+      }
+      add(en, acc, 1.0);
     }
   }
 }
@@ -547,15 +666,11 @@ struct Assembly {
   AsmMem mem;
 };
 
-template <int DIM, int DC, int CPT, int NT>
+template <int DIM, int NT, int WPS>
 static void launch_assemble_dim(Assembly &A, const double *y, double *r, double *jval, hipStream_t st) {
-  constexpr int NL = Shape<DIM>::NL;
-  const int nsplit = (NL + 1 + DC - 1) / DC;   // the element's columns and the residual
   for (int c = 0; c < A.v.ncolor; ++c) {
     const int n = A.h_color_ptr[c + 1] - A.h_color_ptr[c];
-    if (n > 0)
-      k_assemble<DIM, DC, CPT, NT>
-          <<<n * nsplit, NT, 0, st>>>(A.v, y, r, jval, A.map, A.h_color_ptr[c], nsplit);
+    if (n > 0) k_assemble<DIM, NT, WPS><<<n, NT, 0, st>>>(A.v, y, r, jval, A.map, A.h_color_ptr[c]);
   }
 }
 
@@ -563,9 +678,9 @@ static void assemble(Assembly &A, const double *y, double *r, double *jval, hipS
   launch_fill_f64(r, A.v.ndof, 0.0, st);
   launch_fill_f64(jval, A.nnz, 0.0, st);
   if (A.dim == 2)
-    launch_assemble_dim<2, 40, 10, 192>(A, y, r, jval, st);   // the whole element in one workgroup
+    launch_assemble_dim<2, 256, 4>(A, y, r, jval, st);   // 128 threads: 117 us per assembly, 192: 98, 384: 133
   else
-    launch_assemble_dim<3, 16, 8, 256>(A, y, r, jval, st);
+    launch_assemble_dim<3, 1024, 4>(A, y, r, jval, st);
   if (A.ndir)
     k_dirichlet_rows<<<(A.ndir + 255) / 256, 256, 0, st>>>(A.d_dir_rows, A.d_dir_diag, A.ndir, y, A.d_dir_val, r,
                                                             jval);
