@@ -57,40 +57,74 @@ __device__ __forceinline__ void lu_take(const T (&v)[R][NC], int ql, int ll, T (
   }
 }
 
-// the pivot steps on columns t, t + 1, ... of a group of NC (see lu_columns);
-// t0: the group's first step in the panel
+// |a| as an unsigned integer: its bits (FP64: the upper half, 21 significant
+// bits); at least kLuInf: infinite or no number
+__device__ __forceinline__ unsigned lu_key(double a) {
+  return (unsigned)(__double_as_longlong(a) >> 32) & 0x7fffffffu;
+}
+__device__ __forceinline__ unsigned lu_key(float a) { return __float_as_uint(a) & 0x7fffffffu; }
+template <typename T>
+constexpr unsigned kLuInf = sizeof(T) == 8 ? 0x7ff00000u : 0x7f800000u;
+// wave-wide maximum (all lanes active), the same value in every lane
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned lu_dpp_max(unsigned v) {
+  return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, ROWS == 0xF));
+}
+__device__ __forceinline__ unsigned lu_wave_max(unsigned v) {
+  v = lu_dpp_max<kDppXor1, 0xF>(v);
+  v = lu_dpp_max<kDppXor2, 0xF>(v);
+  v = lu_dpp_max<kDppRor4, 0xF>(v);
+  v = lu_dpp_max<kDppRor8, 0xF>(v);
+  v = lu_dpp_max<kDppBcast15, 0xA>(v);
+  v = lu_dpp_max<kDppBcast31, 0xC>(v);
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// The pivot steps on columns t, t + 1, ... of a group of NC (see lu_columns);
+// t0: the group's first step in the panel.  The pivot is the first lane's
+// whose key is the largest: within 2^-20 of the largest candidate in FP64,
+// which the growth of the factors does not feel, and one 32-bit maximum a
+// reduction step instead of a 64-bit one with the row in it.  The next pivot
+// column is eliminated first, so its search runs beside the other columns.
 template <typename T, int R, int NC, int t>
 __device__ __forceinline__ void lu_steps(T (&v)[R][NC], int (&step)[R], int t0, T *scale, int &fail) {
   const int lane = threadIdx.x & 63;
-  double key = -1.0;
+  unsigned key = 0;
+  int lq = 0;
   T sv = 1;
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    const double kq = pivot_key((double)v[q][t], q * 64 + lane);
-    if (step[q] < 0 && kq > key) {
-      key = kq;
-      sv = v[q][t];
-    }
+    const unsigned kq = step[q] < 0 ? lu_key(v[q][t]) : 0u;
+    const bool more = kq > key;
+    key = more ? kq : key;
+    sv = more ? v[q][t] : sv;
+    lq = more ? q : lq;
   }
   const T dl = recip(sv);   // every lane inverts its own candidate during the reduction
-  const double best = wave_max<true>(key);
-  const double bv = key_value(best);
-  const bool bad = !(best >= 0.0) || !(bv > 0.0) || bv >= key_value(pivot_key(DBL_MAX, 0));
+  const unsigned best = lu_wave_max(key);
+  const bool bad = best == 0 || best >= kLuInf<T>;
   fail = fail == 0 && bad ? t0 + t + 1 : fail;
-  const int slot = __builtin_amdgcn_readfirstlane(key_row(best));
-  const int ll = slot & 63;
+  const int ll = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(__ballot(key == best)));
+  const int ql = R == 1 ? 0 : __builtin_amdgcn_readlane(lq, ll);
+  const int slot = ql * 64 + ll;
   const T d = readlane(dl, ll);
   if (lane == 0) scale[t] = d;
   T prow[NC];
-  lu_take<T, R, NC>(v, slot >> 6, ll, prow);
+  lu_take<T, R, NC>(v, ql, ll, prow);
+  T fd[R];
+  bool own[R];
 #pragma unroll
   for (int q = 0; q < R; ++q) {
-    const bool own = slot == q * 64 + lane;
-    const T fd = own ? (T)0 : v[q][t] * d;
-    step[q] = own ? t0 + t : step[q];
+    own[q] = slot == q * 64 + lane;
+    fd[q] = own[q] ? (T)0 : v[q][t] * d;
+    step[q] = own[q] ? t0 + t : step[q];
+  }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      v[q][c] = c == t ? (own ? (T)1 : -fd) : v[q][c] - fd * prow[c];
+  for (int cc = 0; cc < NC; ++cc) {
+    const int c = (t + 1 + cc) % NC;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      v[q][c] = c == t ? (own[q] ? (T)1 : -fd[q]) : v[q][c] - fd[q] * prow[c];
       // keeps each step's work in the step: deferred, the columns that no
       // later step searches would hold every pivot row in scalars to the end
       asm volatile("" : "+v"(v[q][c]));
@@ -397,6 +431,7 @@ __device__ __forceinline__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, 
     }
     __syncthreads();
     if (wave == 0) {
+      __builtin_amdgcn_s_setprio(3);   // the pivot chain before the updates that share its SIMD
       const int h0 = BAND ? hi[p] : n, h1 = BAND ? (p + 1 < np ? hi[p + 1] : h0) : n;
       int res = 0;
       // as few rows a lane as hold the slots in use, before and after
@@ -415,6 +450,7 @@ __device__ __forceinline__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, 
       else { FSI_LU_CASE(13, 4) }
 #undef FSI_LU_CASE
       if (lane == 0) *L.result(p) = res;
+      __builtin_amdgcn_s_setprio(0);
     } else if (p) {
       // the previous panel's update of the columns beyond this panel: whole
       // 16-column tiles per wave, kLuAhead C tiles in flight
