@@ -460,31 +460,32 @@ __device__ __forceinline__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, 
         const int c0 = p0 + 16 + 16 * ct;
         T bx[4];
         load_x(c0, bx);
-        acc ring[kLuAhead];
-        Quad<T> fr[PB == 1 ? kLuAhead : 1];
+        // a tile's rows and factors are fetched with its values
+        struct Tile {
+          int r[4];
+          Quad<T> f;
+          acc c;
+        } ring[kLuAhead];
+        auto fetch = [&](int rt, Tile &t) {
 #pragma unroll
-        for (int u = 0; u < kLuAhead; ++u) {
-          ring[u] = load_c(min(u, nrt - 1), c0);
-          if constexpr (PB == 1) fr[u] = load_f(min(u, nrt - 1));
-        }
+          for (int r = 0; r < 4; ++r) t.r[r] = row[rt * 16 + MM::row(r, kq)];
+          t.f = load_f(rt);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) t.c[r] = A[max(t.r[r], 0) * ld + c0 + jl];
+        };
+#pragma unroll
+        for (int u = 0; u < kLuAhead; ++u) fetch(min(u, nrt - 1), ring[u]);
         for (int rt0 = 0; rt0 < nrt; rt0 += kLuAhead) {
 #pragma unroll
           for (int u = 0; u < kLuAhead; ++u) {
             const int rt = rt0 + u;
             if (rt < nrt) {
-              acc c;
-              if constexpr (PB == 1) {
-                c = update(fr[u], bx, ring[u]);
-                fr[u] = load_f(min(rt + kLuAhead, nrt - 1));
-              } else {
-                c = update(load_f(rt), bx, ring[u]);
-              }
-              ring[u] = load_c(min(rt + kLuAhead, nrt - 1), c0);
+              Tile &t = ring[u];
+              const acc c = update(t.f, bx, t.c);
 #pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int i = row[rt * 16 + MM::row(r, kq)];
-                if (i >= 0) A[i * ld + c0 + jl] = c[r];
-              }
+              for (int r = 0; r < 4; ++r)
+                if (t.r[r] >= 0) A[t.r[r] * ld + c0 + jl] = c[r];
+              fetch(min(rt + kLuAhead, nrt - 1), t);
             }
           }
         }
