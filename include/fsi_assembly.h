@@ -41,8 +41,9 @@ fsi_status fsi_assembly_create(const fsi_element_data *ed, const fsi_csr *J, voi
 /* r = R(y) (ndof doubles) and the values of J = dR/dy in the pattern's order
  * (nnz doubles), all device arrays, stream-ordered on hip_stream.  Dirichlet
  * rows: r_i = y_i - g_i and a unit diagonal.  One launch per element colour:
- * the element residual's per-point coefficients differentiated along each
- * local dof (forward mode), then contracted with the test functions; every
+ * the element residual's per-point coefficients differentiated along the
+ * point's field sums (forward mode), then multiplied with the test-function
+ * tables from both sides; every
  * entry is written by one thread per colour (no atomics, the same result
  * every run).
  * Errors: FSI_E_INVALID (null), FSI_E_DEVICE. */

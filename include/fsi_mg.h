@@ -52,7 +52,7 @@ enum {
 /* Precision of the V-cycle (the Krylov method, the true residual and the
  * coarsest solve are always FP64).  FP64: blocks inverted and applied in
  * FP64.  MIXED_*: V-cycle vectors, operators and transfers in FP32; the
- * blocks are inverted in FP32 (Gauss-Jordan on the FP32 matrix cores) and
+ * blocks are inverted in FP32 (on the FP32 matrix cores) and
  * the owned rows of each inverse stored in the named 16-bit type with
  * two-sided FP32 scaling (B^{-1} = diag(rs) W diag(cs)) and applied with FP32
  * accumulation; MIXED_FP32: owned rows stored in FP32. */
@@ -161,10 +161,10 @@ const char *fsi_last_error(void);
  * operators, transfers) and "Richardson-Schwarz smoother" (blocks B_k =
  * R^delta_k J R^delta_k^T solved exactly, restricted write-back R^0_k).
  * Uploads the hierarchy, extracts B_k = J_l[I_k, I_k] for every patch, inverts
- * it (Gauss-Jordan, partial pivoting; the paper's local direct solve) keeping
+ * it (LU or Gauss-Jordan, partial pivoting; the paper's local direct solve) keeping
  * the rows selected by R^0_k, and inverts the coarsest operator (its dofs
  * whose row and column hold only the diagonal, the eliminated Dirichlet dofs,
- * by a reciprocal, the others by Gauss-Jordan; the sparsity pattern decides,
+ * by a reciprocal, the others by elimination; the sparsity pattern decides,
  * so a refactor keeps the split).  Blocks of up to 800 dofs are inverted
  * together in one batched launch; larger ones (up to 6144 dofs, such as the
  * 3D 64-element patches) one after another, each by a chain of launches over
