@@ -37,6 +37,7 @@ def ras_bytes(info, wbytes, vbytes):
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "ras_finest_c1_2d_128x32_fp64_traffic.md")
 GJ_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "gj_batched_c1_2d_128x32_fp64_traffic.md")
+LU_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "lu_blocks_c1_2d_128x32_fp64_traffic.md")
 CSRC = os.path.join(ROOT, "paper_1709_05660_amd", "csrc")
 
 
@@ -55,6 +56,12 @@ def gj_kernel_digest():
     src = open(os.path.join(CSRC, "fsi_gj.hip")).read()
     b = src.index("static size_t gj_batched_lds")
     return hashlib.sha256(src[:b].encode()).hexdigest()[:16]
+
+
+def lu_kernel_digest():
+    """Digest of the device code of the blocks' LU inversion."""
+    src = open(os.path.join(CSRC, "fsi_lu.hip")).read()
+    return hashlib.sha256(src[:src.index("static void launch_blocks(")].encode()).hexdigest()[:16]
 
 
 def measured_traffic(path=TRAFFIC_PROFILE, digest=ras_kernel_digest, variant=None):
@@ -545,7 +552,8 @@ def gpu_leg(args):
         out["roofline"] = {
             "bound": "mfma", "kernel": kernel + " inverse of all 336 Schwarz blocks, FP64 matrix cores)",
             "achieved": round(gj_tflops, 3), "peak": 78.6, "unit": "TFLOP/s",
-            "frac": round(gj_tflops / 78.6, 4), "traffic": measured_traffic(GJ_TRAFFIC_PROFILE, gj_kernel_digest, vid),
+            "frac": round(gj_tflops / 78.6, 4), "traffic": (measured_traffic(LU_TRAFFIC_PROFILE, lu_kernel_digest, vid) if vid == 7 else
+                                                  measured_traffic(GJ_TRAFFIC_PROFILE, gj_kernel_digest, vid)),
             "flops_per_launch": lu_flops, "flop_count": "2/3 sum m_k^3 (LU-equivalent work of the local solves)",
             "gauss_jordan_flops_per_launch": gj_flops,
             "frac_on_gauss_jordan_flops": round(gj_flops / (gj_avg_ms * 1e-3) / 1e12 / 78.6, 4) if gcnt else None,
