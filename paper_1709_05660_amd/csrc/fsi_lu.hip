@@ -910,9 +910,9 @@ __global__ __launch_bounds__(256) void k_scale_rows(int n, const int *__restrict
 }
 
 // One workgroup per block, the largest first.  Up to 372 dofs (336 blocks, more
-// than compute units) it is bound by the updates' traffic: 4.9 GB in 1.15 ms in
-// FP64, 4.2 TB/s, a plain copy's rate; one block alone takes 0.39 ms, the chain
-// of pivot steps (0.75 us each at six rows a lane).  Larger blocks (one
+// than compute units) it is bound by the updates' traffic: 4.9 GB in 1.11 ms in
+// FP64, 4.4 TB/s, a plain copy's rate; one block alone takes 0.35 ms, the chain
+// of pivot steps.  Larger blocks (one
 // workgroup to a compute unit) are bound by that chain.
 template <typename T, int RMAX, int PB>
 __global__ __launch_bounds__(kLuThreads) void k_lu_blocks(T *__restrict__ blocks, const int64_t *__restrict__ boff,

@@ -914,10 +914,10 @@ static void invert_large(MG &mg, hipStream_t st) {
 // search needs no workgroup barrier, a third of the entries is updated, and
 // only the rows the V-cycle uses are formed.  Factors and packed rows against
 // the best Gauss-Jordan variant with packing: 336 blocks of the 128x32 system
-// (up to 372 dofs) 1.15 + 0.67 ms against 3.05 + 0.32 in FP64, 0.74 + 0.37 +
+// (up to 372 dofs) 1.11 + 0.67 ms against 3.05 + 0.32 in FP64, 0.74 + 0.37 +
 // 0.14 (16-bit) against 2.24 + 0.36 in FP32; 288 blocks of the 32x8x8 system
-// (up to 637 dofs) in FP32 4.1 + 1.1 + 0.2 against 9.5 + 0.7; the 32 of
-// 16x4x4 (FP64, up to 490) 1.15 + 0.25 against 2.7 + 0.1.
+// (up to 637 dofs) in FP32 3.9 + 1.1 + 0.2 against 9.5 + 0.7; the 32 of
+// 16x4x4 (FP64, up to 490) 1.06 + 0.25 against 2.7 + 0.1.
 static bool lu_possible(const MG &mg) {
   return mg.large.empty() && mg.lu_nblk > 0;
 }
