@@ -363,7 +363,8 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
 // columns [n, ld) zero; base 16-byte aligned).  Banded: rows sorted by their
 // first column; before panel p the rows [0, hi[p]) may be nonzero in its
 // columns, and their last column is below cend[p]; at most nslot rows wait at
-// a time.  nslot: slots in LDS, a multiple of 16.
+// a time, at least one before each panel (hi[p] > 16 p: BandOrder::full).
+// nslot: slots in LDS, a multiple of 16.
 template <typename T, int RMAX, bool BAND, int PB>
 __device__ __forceinline__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, const int *__restrict__ hi,
                           const int *__restrict__ cend, int nslot, int *__restrict__ perm, int *__restrict__ plo,
@@ -455,7 +456,8 @@ __device__ __forceinline__ void lu_matrix(T *__restrict__ A, int n, int64_t ld, 
       // the previous panel's update of the columns beyond this panel: whole
       // 16-column tiles per wave, kLuAhead C tiles in flight
       const int ce = BAND ? cend[p - 1] : n;
-      const int nct = (ce - p0 - 1) >> 4;   // tiles that start in [p0 + 16, ce)
+      // tiles that start in [p0 + 16, ce); none without a row to update
+      const int nct = nrt ? (ce - p0 - 1) >> 4 : 0;
       for (int ct = wave - 1; ct < nct; ct += kLuWaves - 1) {
         const int c0 = p0 + 16 + 16 * ct;
         T bx[4];

@@ -89,6 +89,7 @@ void panels(int n, const std::vector<int64_t> &rowptr, const std::vector<int> &c
     for (; row < b.hi[p]; ++row) end = std::max(end, lastof[row] + 1);
     b.cend[p] = std::max(end, std::min((p + 1) * nb, n));
     b.window = std::max(b.window, b.hi[p] - p * nb);
+    b.full = b.full && b.hi[p] >= std::min((p + 1) * nb, n);
   }
 }
 
@@ -131,7 +132,9 @@ BandOrder band_order(int n, const std::vector<int64_t> &rowptr, const std::vecto
     b.colpos.resize(n);
     for (int k = 0; k < n; ++k) b.colpos[order[dir][k]] = k;
     panels(n, rowptr, colind, nb, b);
+    const bool full = b.full;   // (singular in one direction, singular in both)
     if (!dir || b.window < best.window) best = std::move(b);
+    best.full = best.full && full;
   }
   return best;
 }
