@@ -557,17 +557,21 @@ __global__ __launch_bounds__(256) void k_equil(int n, const int *__restrict__ ro
 }
 
 // the scaled free block into its ordered places (zero-filled beforehand); one
-// wave per row
+// wave per row.  An entry that is not finite fails the operator here (status:
+// 1 + its column's step): only the rows that wait together with its row take
+// its column's update, so where the window empties no pivot would show it.
 __global__ __launch_bounds__(256) void k_band_dense(int n, int64_t ld, const int *__restrict__ rowptr,
                                                     const int *__restrict__ col, const double *__restrict__ val,
                                                     const int *__restrict__ rpos, const int *__restrict__ cpos,
                                                     const int *__restrict__ er, const int *__restrict__ cmax,
-                                                    double *__restrict__ A) {
+                                                    double *__restrict__ A, int *__restrict__ status) {
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= n || rpos[r] < 0) return;
   for (int p = rowptr[r] + (threadIdx.x & 63); p < rowptr[r + 1]; p += 64) {
     const int c = cpos[col[p]];
-    if (c >= 0) A[rpos[r] * ld + c] = ldexp(val[p], er[r] + col_exp(cmax, n, col[p], kEquilSteps));
+    if (c < 0) continue;
+    if (!(fabs(val[p]) <= DBL_MAX)) atomicMax(status, 1 + c);
+    A[rpos[r] * ld + c] = ldexp(val[p], er[r] + col_exp(cmax, n, col[p], kEquilSteps));
   }
 }
 
@@ -579,6 +583,7 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_band(double *__restrict__ A, 
                                                         int nslot, int *__restrict__ perm, int *__restrict__ plo,
                                                         int *__restrict__ status) {
   extern __shared__ __align__(16) unsigned char lu_lds[];
+  if (status[0]) return;   // an entry that is not finite
   lu_matrix<double, RMAX, true, 2>(A, n, ld, hi, cend, nslot, perm, plo, status, lu_lds);
 }
 
@@ -866,7 +871,8 @@ void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &
   for (int k = 0; k < kEquilSteps; ++k)
     k_equil<<<wg, 256, 0, st>>>(cs.n, J.rowptr, J.col, J.val, cs.fpos, k, er, cmax);
   launch_fill_f64(A, (int64_t)B.n * ld, 0.0, st);
-  k_band_dense<<<wg, 256, 0, st>>>(cs.n, ld, J.rowptr, J.col, J.val, B.rpos, B.cpos, er, cmax, A);
+  k_band_dense<<<wg, 256, 0, st>>>(cs.n, ld, J.rowptr, J.col, J.val, B.rpos, B.cpos, er, cmax, A,
+                                   status);
   if (B.nslot <= 128)
     launch_band_factor<2>(A, B, ld, status, st);
   else if (B.nslot <= 256)
