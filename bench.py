@@ -61,7 +61,7 @@ def gj_kernel_digest():
 def lu_kernel_digest():
     """Digest of the device code of the blocks' LU inversion."""
     src = open(os.path.join(CSRC, "fsi_lu.hip")).read()
-    return hashlib.sha256(src[:src.index("static void launch_blocks(")].encode()).hexdigest()[:16]
+    return hashlib.sha256(src[:src.index("static auto lu_blocks_class(")].encode()).hexdigest()[:16]
 
 
 def measured_traffic(path=TRAFFIC_PROFILE, digest=ras_kernel_digest, variant=None):

@@ -639,9 +639,11 @@ static void launch_gj_nbr(T *blocks, const int64_t *boff, const int *pm, const i
                           int *perm, int *used, int grid, const int *sched, int mmax, int *status,
                           hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
   const size_t shm = GPC ? 0 : gj_batched_lds(mmax, NB, sizeof(T));
-  if (shm)
-    (void)hipFuncSetAttribute((const void *)k_gj_batched<T, NB, R, NT, UNR, GPC>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+  if (shm) {   // all that the static LDS leaves (a failed call: the launch reports it)
+    static std::atomic<uint64_t> devices{0};
+    const int64_t own = gj_static_lds<T, NB, R, NT, UNR>();
+    (void)allow_lds(devices, (const void *)k_gj_batched<T, NB, R, NT, UNR, GPC>, 160 * 1024 - std::max<int64_t>(own, 0));
+  }
   // with events: recorded at the kernel's own start and end
   hipExtLaunchKernelGGL(k_gj_batched<T, NB, R, NT, UNR, GPC>, dim3(grid), dim3(NT), shm, st, ev0, ev1, 0,
                         blocks, boff, pm, poff, perm, used, status, sched);

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
 #include <vector>
 
 namespace fsi {
@@ -16,6 +17,13 @@ constexpr int kMaxLargePatch = 6144;   // larger blocks: one Gauss-Jordan chain 
 // inversions have rows of a multiple of 16 entries (whole aligned 16-column
 // tiles; the padding stays zero until the inversion), larger ones are packed.
 __host__ __device__ __forceinline__ constexpr int block_ld(int m) { return m <= kMaxPatch ? (m + 15) / 16 * 16 : m; }
+
+// Raises the dynamic LDS limit of a kernel to `bytes` on the current device,
+// once per device (devices: those done, one static mask per kernel instance).
+// The limit is the kernel's, shared by handles of every size and by setup
+// threads: bytes is the most that any launch of the instance takes, so that
+// no handle lowers it under another's launch.
+hipError_t allow_lds(std::atomic<uint64_t> &devices, const void *kernel, size_t bytes);
 
 // CSR on the device: int32 offsets and columns (sizes checked at upload).
 template <typename T>
@@ -108,6 +116,9 @@ struct LuRowsBatch {
   int task0[kLuRowsItems + 1];
   LuRowsItem<T> it[kLuRowsItems];
 };
+// LDS limit for launch_lu_blocks on the current device, before its first call
+template <typename T>
+hipError_t lu_blocks_prepare(int mmax);
 template <typename T>
 void launch_lu_blocks(T *blocks, const int64_t *boff, const int *pm, const int64_t *poff, int *perm, int *status,
                       const int *order, int nblk, int mmax, hipStream_t st, hipEvent_t ev0 = nullptr);
@@ -155,8 +166,8 @@ struct BandView {
 constexpr int kEquilSteps = 4;
 constexpr int kLuBandSlots = 384;    // waiting rows at most (six a lane of the factoring wave)
 constexpr int kLuBandMax = 2560;     // largest ordered block (20 panels a wave in k_lu_band_rows)
-// once before the first lu_coarse (which may be captured into a graph)
-void lu_coarse_prepare();
+// LDS limit for lu_coarse on the current device, before its first call (which may be captured into a graph)
+hipError_t lu_coarse_prepare(int nslot);
 // as gj_coarse, from the operator itself; A: work of n rows of ld doubles (a
 // multiple of 16)
 void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &J, const CoarseSplit &cs, double *C0,

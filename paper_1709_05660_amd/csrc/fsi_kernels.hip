@@ -11,13 +11,24 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
-#include <mutex>
 #include <type_traits>
 #include <cmath>
 
 namespace fsi {
 
 static inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+hipError_t allow_lds(std::atomic<uint64_t> &devices, const void *kernel, size_t bytes) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;   // devices past the mask: set each time
+  if (e == hipSuccess && !(devices.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) devices.fetch_or(bit, std::memory_order_release);
+  }
+  if (e != hipSuccess) (void)hipGetLastError();   // the caller's to report, not the next launch check's
+  return e;
+}
 
 // ------------------------------------------------------------------ SpMV
 // Sum over a group of LPR consecutive lanes, the total in every lane of the
@@ -946,11 +957,6 @@ void launch_ras_batch_16(const RasItem<uint16_t, float> *items, int count, float
 }
 
 // ------------------------------------------------------------------ ILU(0) of fluid blocks
-// a failed attribute call must not leave its error for the next launch check
-static inline void hip_ok_or_clear(hipError_t e) {
-  if (e != hipSuccess) (void)hipGetLastError();
-}
-
 // Right-looking elimination on the dense block with the pattern as a mask,
 // one workgroup per block: step k updates a_ij -= (a_ik / a_kk) a_kj at the
 // pattern positions (i, j) with i, j > k, a_ik and a_kj in the pattern (the
@@ -1129,11 +1135,8 @@ void launch_ilu_apply(const IluView &v, const V *lval, const V *uval, const V *u
   constexpr size_t kStageMax = 128 * 1024;
   const size_t stage = (size_t)v.max_entries * (sizeof(V) + sizeof(int16_t));
   if (stage <= kStageMax) {
-    static std::once_flag attr;   // raise the dynamic LDS limit once per instance (setup threads race here)
-    std::call_once(attr, [] {
-      hip_ok_or_clear(hipFuncSetAttribute((const void *)k_ilu_apply<V, true>,
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStageMax));
-    });
+    static std::atomic<uint64_t> devices{0};
+    (void)allow_lds(devices, (const void *)k_ilu_apply<V, true>, kStageMax);   // (failed: the launch reports it)
     k_ilu_apply<V, true><<<v.nblk, 256, stage, st>>>(v, lval, uval, udiag, s, e, omega, (int)add, (int)clear);
   } else {
     k_ilu_apply<V, false><<<v.nblk, 256, 0, st>>>(v, lval, uval, udiag, s, e, omega, (int)add, (int)clear);

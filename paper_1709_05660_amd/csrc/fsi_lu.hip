@@ -25,7 +25,7 @@
 
 #include <algorithm>
 #include <climits>
-#include <mutex>
+#include <type_traits>
 
 #include "fsi_kernels.h"
 #include "fsi_pivot.h"
@@ -850,17 +850,13 @@ static void launch_band_rows(const double *A, const BandView &B, int64_t ld, con
 }
 
 template <int RMAX>
-static void allow_band_lds() {
-  (void)hipFuncSetAttribute((const void *)k_lu_band<RMAX>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lu_lds_bytes<double>(std::min(64 * RMAX, kLuBandSlots), 2));
+static hipError_t allow_band_lds() {
+  static std::atomic<uint64_t> devices{0};
+  return allow_lds(devices, (const void *)k_lu_band<RMAX>,
+                   lu_lds_bytes<double>(std::min(64 * RMAX, kLuBandSlots), 2));
 }
-void lu_coarse_prepare() {
-  static std::once_flag once;   // setup threads may come together
-  std::call_once(once, [] {
-    allow_band_lds<2>();
-    allow_band_lds<4>();
-    allow_band_lds<6>();
-  });
+hipError_t lu_coarse_prepare(int nslot) {
+  return nslot <= 128 ? allow_band_lds<2>() : nslot <= 256 ? allow_band_lds<4>() : allow_band_lds<6>();
 }
 
 void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &J, const CoarseSplit &cs, double *C0,
@@ -1062,31 +1058,36 @@ __global__ __launch_bounds__(256) void k_pack16_rows(const float *__restrict__ r
   }
 }
 
-template <typename T, int RMAX, int PB = 2>
-static void launch_blocks(T *blocks, const int64_t *boff, const int *pm, const int64_t *poff, int *perm, int *status,
-                          const int *order, int nblk, int mmax, hipStream_t st, hipEvent_t ev0) {
-  const size_t shm = lu_lds_bytes<T>(block_ld(mmax), PB);
-  (void)hipFuncSetAttribute((const void *)k_lu_blocks<T, RMAX, PB>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)shm);
-  hipExtLaunchKernelGGL((k_lu_blocks<T, RMAX, PB>), dim3(nblk), dim3(kLuThreads), shm, st, ev0, nullptr, 0, blocks,
-                        boff, pm, poff, perm, status, order);
+// The instance for blocks of up to mmax dofs, to f as its rows a lane of the
+// factoring wave (registers for the largest block) and panel buffers (two of
+// more than 512 FP64 rows do not fit in LDS).
+template <typename T, class F>
+static auto lu_blocks_class(int mmax, F f) {
+  if (mmax <= 128) return f(std::integral_constant<int, 2>(), std::integral_constant<int, 2>());
+  if (mmax <= 256) return f(std::integral_constant<int, 4>(), std::integral_constant<int, 2>());
+  if (mmax <= 384) return f(std::integral_constant<int, 6>(), std::integral_constant<int, 2>());
+  if (mmax <= 512) return f(std::integral_constant<int, 8>(), std::integral_constant<int, 2>());
+  return f(std::integral_constant<int, 13>(), std::integral_constant<int, sizeof(T) == 8 ? 1 : 2>());
 }
+template <typename T>
+hipError_t lu_blocks_prepare(int mmax) {
+  return lu_blocks_class<T>(mmax, [](auto rmax, auto pb) {
+    static std::atomic<uint64_t> devices{0};
+    return allow_lds(devices, (const void *)k_lu_blocks<T, rmax(), pb()>,
+                     lu_lds_bytes<T>(block_ld(std::min(64 * rmax(), kMaxPatch)), pb()));
+  });
+}
+template hipError_t lu_blocks_prepare<double>(int);
+template hipError_t lu_blocks_prepare<float>(int);
 template <typename T>
 void launch_lu_blocks(T *blocks, const int64_t *boff, const int *pm, const int64_t *poff, int *perm, int *status,
                       const int *order, int nblk, int mmax, hipStream_t st, hipEvent_t ev0) {
   if (nblk == 0) return;
-  // rows a lane of the factoring wave: registers for the largest block; two
-  // panels of more than 512 FP64 rows do not fit in LDS
-  if (mmax <= 128)
-    launch_blocks<T, 2>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
-  else if (mmax <= 256)
-    launch_blocks<T, 4>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
-  else if (mmax <= 384)
-    launch_blocks<T, 6>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
-  else if (mmax <= 512)
-    launch_blocks<T, 8>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
-  else
-    launch_blocks<T, 13, sizeof(T) == 8 ? 1 : 2>(blocks, boff, pm, poff, perm, status, order, nblk, mmax, st, ev0);
+  lu_blocks_class<T>(mmax, [&](auto rmax, auto pb) {
+    hipExtLaunchKernelGGL((k_lu_blocks<T, rmax(), pb()>), dim3(nblk), dim3(kLuThreads),
+                          lu_lds_bytes<T>(block_ld(mmax), pb()), st, ev0, nullptr, 0, blocks, boff, pm, poff, perm,
+                          status, order);
+  });
 }
 template void launch_lu_blocks<double>(double *, const int64_t *, const int *, const int64_t *, int *, int *,
                                        const int *, int, int, hipStream_t, hipEvent_t);

@@ -806,7 +806,7 @@ static void plan_band(MG &mg, const fsi_csr &J, const std::vector<int> &fpos, hi
     rowdof[b.rowpos[f]] = dof[f];
     coldof[b.colpos[f]] = dof[f];
   }
-  lu_coarse_prepare();
+  hip_check(lu_coarse_prepare(nslot), "LDS limit of the coarsest elimination");
   mg.band.rpos = dupload(rpos.data(), (int64_t)rpos.size(), mg.owned, st);
   mg.band.cpos = dupload(cpos.data(), (int64_t)cpos.size(), mg.owned, st);
   mg.band.scale = dalloc<int>((kEquilSteps + 1) * (int64_t)J.nrows, mg.owned);
@@ -1771,6 +1771,9 @@ MG *mg_setup(const fsi_level *levels, int nlevels, const fsi_mg_opts *opts, hipS
       std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return all_pm[a] > all_pm[b]; });
       mg->lu_nblk = (int)order.size();
       mg->lu_order = dupload(order.data(), mg->lu_nblk, mg->owned, st);
+      if (lu_possible(*mg))
+        hip_check(mg->mixed ? lu_blocks_prepare<float>(mg->mmax_all) : lu_blocks_prepare<double>(mg->mmax_all),
+                  "LDS limit of the blocks' elimination");
     }
     mg->gj_perm = dalloc<int>(std::max<int64_t>(pbase, 1), mg->owned);
     mg->gj_used = dalloc<int>(std::max<int64_t>(pbase, 1), mg->owned);
