@@ -165,7 +165,11 @@ struct BandView {
 };
 constexpr int kEquilSteps = 4;
 constexpr int kLuBandSlots = 384;    // waiting rows at most (six a lane of the factoring wave)
-constexpr int kLuBandMax = 2560;     // largest ordered block (20 panels a wave in k_lu_band_rows)
+constexpr int kLuBandMax = 2560;     // largest ordered block
+constexpr int kLuBandWindow = 8;     // tiles a wave in registers in k_lu_band_rows_long
+// whether the inverse's rows can be found from factors whose panels' columns
+// end at cend (in k_lu_band_rows_long a panel updates tiles in registers only)
+bool lu_band_reach_ok(const int *cend, int n);
 // LDS limit for lu_coarse on the current device, before its first call (which may be captured into a graph)
 hipError_t lu_coarse_prepare(int nslot);
 // as gj_coarse, from the operator itself; A: work of n rows of ld doubles (a

@@ -827,6 +827,228 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_band_rows(const double *__res
     }
 }
 
+// The same for a matrix of more panels than a wave holds tiles of.  Each wave
+// keeps in registers the TPW of its tiles around the current panel: slot u is
+// tile 8 (p / 8 + u) + wave going forward, 8 (p / 8 - u) + wave going back, and
+// the slots move up by one every eight panels.  Forward no panel reaches
+// further (the host has checked cend); back, a row that waited long has factors
+// in panels before the window, whose tiles are then updated in memory.  A tile
+// outside the window lies in its final place in C0, unscaled until z is final,
+// and always by the same lanes; `kept` marks this wave's tiles that are there
+// (the others are zero).  2,522 unknowns: 851 us, 178 registers; with all 20
+// tiles of a wave in registers 1,485 of them spilled, 1,584 us.
+template <int TPW, int TA>
+__global__ __launch_bounds__(kLuThreads) void k_lu_band_rows_long(const double *__restrict__ A, int n, int ld,
+                                                                  const int *__restrict__ perm,
+                                                                  const int *__restrict__ plo,
+                                                                  const int *__restrict__ cend,
+                                                                  const int *__restrict__ status,
+                                                                  const int *__restrict__ rowdof,
+                                                                  const int *__restrict__ coldof,
+                                                                  const int *__restrict__ er,
+                                                                  const int *__restrict__ cmax, int n0, double *C0) {
+  typedef Mfma16<double> MM;
+  // a slot's preloaded factors keep their place when the slots move
+  static_assert(TA + 2 <= TPW && TPW % TA == 0 && kLuBandMax <= 64 * kLuWaves * kLuNb, "");
+  __shared__ double bc[2 * 256];
+  __shared__ int prow[kLuBandMax];
+  if (status[0]) return;
+  const int lane = threadIdx.x & 63, jl = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.x, np = (n + kLuNb - 1) / kLuNb;
+  for (int s = threadIdx.x; s < np * kLuNb; s += kLuThreads) prow[s] = min(max(perm[min(s, n - 1)], 0), n - 1);
+  __syncthreads();
+  const bool mine = b * kLuNb + jl < n;   // this lane's unknown
+  const int k = coldof[min(b * kLuNb + jl, n - 1)], ec = col_exp(cmax, n0, k, kEquilSteps);
+  double *C = C0 + (int64_t)k * n0;
+  auto load_a = [&](int p, int j, double (&a)[4]) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) a[kk] = A[prow[p * kLuNb + MM::row(kk, kq)] * ld + j * kLuNb + jl];
+  };
+  auto apply = [&](const double (&a)[4], const dx4 &y, dx4 &z) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) z = MM::mma(a[kk], y[kk], z);
+  };
+  auto publish = [&](int p, const dx4 &y) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bc[(p & 1) * 256 + r * 64 + lane] = y[r];
+  };
+  auto fetch = [&](int p) {
+    dx4 y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = bc[(p & 1) * 256 + r * 64 + lane];
+    return y;
+  };
+  uint64_t kept = 0;
+  auto put = [&](int j, const dx4 &z, bool last) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int s = j * kLuNb + MM::row(r, kq);
+      if (mine && s < n) {
+        const int c = rowdof[prow[s]];
+        C[c] = last ? ldexp(z[r], ec + er[c]) : z[r];
+      }
+    }
+    kept |= 1ull << (j / kLuWaves);
+  };
+  auto get = [&](int j) {
+    dx4 z = {0, 0, 0, 0};
+    if (j >= 0 && ((kept >> (j / kLuWaves)) & 1)) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int s = j * kLuNb + MM::row(r, kq);
+        if (mine && s < n) z[r] = C[rowdof[prow[s]]];
+      }
+    }
+    return z;
+  };
+  dx4 x[TPW];
+  double a[TA][4], an[TA][4];
+#pragma unroll
+  for (int i = 0; i < TA; ++i)
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) a[i][kk] = an[i][kk] = 0;
+  // the slots moved up by one, the preloaded factors with them
+  auto move = [&](const dx4 &in) {
+#pragma unroll
+    for (int u = 0; u + 1 < TPW; ++u) x[u] = x[u + 1];
+    x[TPW - 1] = in;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const double t = a[0][kk];
+#pragma unroll
+      for (int i = 0; i + 1 < TA; ++i) a[i][kk] = a[i + 1][kk];
+      a[TA - 1][kk] = t;
+    }
+  };
+  auto take_next = [&] {
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) a[i][kk] = an[i][kk];
+  };
+  // tile j of slot u by panel p: its factors preloaded in the first TA slots from u0 on
+  auto apply_slot = [&](int u, int u0, int p, int j, const dx4 &y) {
+    if (u - u0 < TA) {
+      apply(a[u % TA], y, x[u]);
+    } else {
+      double t[4];
+      load_a(p, j, t);
+      apply(t, y, x[u]);
+    }
+  };
+  // forward: w_p from the finished right-hand side in slot u
+  double ad[4] = {0, 0, 0, 0};   // B^-1 of this wave's next panel
+  auto finish = [&](int u, int p) {
+    dx4 y = {0, 0, 0, 0};
+    apply(ad, x[u], y);
+    put(p, y, false);
+    publish(p, -y);
+    if (p + kLuWaves < np) load_a(p + kLuWaves, p + kLuWaves, ad);
+  };
+  auto fwd_first = [&](int p, int v0) { return kLuWaves * v0 + wave > p ? 0 : kLuWaves * (v0 + 1) + wave > p ? 1 : 2; };
+  auto fwd_load = [&](int p, int v0, int jh) {
+    const int u0 = fwd_first(p, v0);
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+      const int j = kLuWaves * (v0 + u) + wave;
+      if (u >= u0 && u - u0 < TA && j < jh) load_a(p, j, an[u % TA]);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) x[u] = dx4{0, 0, 0, 0};
+  if (wave == (b & (kLuWaves - 1)))
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[0][r] = jl == MM::row(r, kq) ? 1.0 : 0.0;
+  {
+    const int own = b + ((wave - b) & (kLuWaves - 1));   // this wave's first panel
+    if (own < np) load_a(own, own, ad);
+  }
+  auto end_of = [&](int p) { return min((cend[p] + kLuNb - 1) / kLuNb, np); };
+  int jh = end_of(b);
+  fwd_load(b, b / kLuWaves, jh);
+  take_next();
+  if (wave == (b & (kLuWaves - 1))) finish(0, b);
+  for (int p = b; p + 1 < np; ++p) {
+    const int v0 = p / kLuWaves, jhn = end_of(p + 1);
+    if (p > b && (p & (kLuWaves - 1)) == 0) move(dx4{0, 0, 0, 0});
+    __syncthreads();
+    const dx4 y = fetch(p);
+    const int u0 = fwd_first(p, v0);
+    if (wave == ((p + 1) & (kLuWaves - 1))) {
+      if (wave) {
+        if (p + 1 < jh) apply_slot(0, u0, p, p + 1, y);
+        finish(0, p + 1);
+      } else {
+        if (p + 1 < jh) apply_slot(1, u0, p, p + 1, y);
+        finish(1, p + 1);
+      }
+    }
+    if (p + 2 < np) fwd_load(p + 1, v0, jhn);
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+      const int j = kLuWaves * (v0 + u) + wave;
+      if (j > p + 1 && j < jh) apply_slot(u, u0, p, j, y);
+    }
+    jh = jhn;
+    take_next();
+  }
+  __syncthreads();   // the broadcast buffers are reused from the last panel down
+  auto back_first = [&](int p, int v0) { return kLuWaves * v0 + wave < p ? 0 : kLuWaves * (v0 - 1) + wave < p ? 1 : 2; };
+  auto back_load = [&](int p, int v0, int j0) {
+    const int u0 = back_first(p, v0);
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+      const int j = kLuWaves * (v0 - u) + wave;
+      if (u >= u0 && u - u0 < TA && j >= j0) load_a(p, j, an[u % TA]);
+    }
+  };
+  const int vl = (np - 1) / kLuWaves;
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) x[u] = get(kLuWaves * (vl - u) + wave);
+  int j0 = plo[np - 1];
+  back_load(np - 1, vl, j0);
+  take_next();
+  if (wave == ((np - 1) & (kLuWaves - 1))) {
+    put(np - 1, x[0], true);
+    publish(np - 1, x[0]);
+  }
+  for (int p = np - 1; p > 0; --p) {
+    const int v0 = p / kLuWaves, j0n = plo[p - 1];
+    if (p < np - 1 && (p & (kLuWaves - 1)) == kLuWaves - 1) move(get(kLuWaves * (v0 - TPW + 1) + wave));
+    __syncthreads();
+    const dx4 y = fetch(p);
+    const int u0 = back_first(p, v0);
+    if (wave == ((p - 1) & (kLuWaves - 1))) {
+      const int j = p - 1;
+      if (wave != kLuWaves - 1) {
+        if (j >= j0) apply_slot(0, u0, p, j, y);
+        put(j, x[0], true);
+        publish(j, x[0]);
+      } else {
+        if (j >= j0) apply_slot(1, u0, p, j, y);
+        put(j, x[1], true);
+        publish(j, x[1]);
+      }
+    }
+    if (p > 1) back_load(p - 1, v0, j0n);
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+      const int j = kLuWaves * (v0 - u) + wave;
+      if (j < p - 1 && j >= j0) apply_slot(u, u0, p, j, y);
+    }
+    for (int j = kLuWaves * (v0 - TPW) + wave; j >= j0; j -= kLuWaves) {
+      dx4 z = get(j);
+      double t[4];
+      load_a(p, j, t);
+      apply(t, y, z);
+      put(j, z, false);
+    }
+    j0 = j0n;
+    take_next();
+  }
+}
+
 // C0 outside the free block: 1 / a_dd on the diagonal of D, zero elsewhere
 __global__ __launch_bounds__(256) void k_coarse_border(int n, const int *__restrict__ fpos,
                                                        const int *__restrict__ rowptr,
@@ -859,6 +1081,16 @@ hipError_t lu_coarse_prepare(int nslot) {
   return nslot <= 128 ? allow_band_lds<2>() : nslot <= 256 ? allow_band_lds<4>() : allow_band_lds<6>();
 }
 
+// panels of which each wave keeps all its tiles (k_lu_band_rows)
+constexpr int kLuBandResident = 9 * kLuWaves;
+bool lu_band_reach_ok(const int *cend, int n) {
+  const int np = (n + kLuNb - 1) / kLuNb;
+  if (np <= kLuBandResident) return true;
+  for (int p = 0; p < np; ++p)
+    if ((cend[p] - 1) / kLuNb / kLuWaves - p / kLuWaves >= kLuBandWindow) return false;
+  return true;
+}
+
 void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &J, const CoarseSplit &cs, double *C0,
                int *status, hipStream_t st) {
   int *er = B.scale, *cmax = B.scale + cs.n;
@@ -875,13 +1107,15 @@ void lu_coarse(double *A, int64_t ld, const BandView &B, const CsrView<double> &
     launch_band_factor<4>(A, B, ld, status, st);
   else
     launch_band_factor<6>(A, B, ld, status, st);
-  const int np = (B.n + kLuNb - 1) / kLuNb, tpw = (np + kLuWaves - 1) / kLuWaves;
-  if (tpw <= 4)
+  const int np = (B.n + kLuNb - 1) / kLuNb;
+  if (np <= 4 * kLuWaves)
     launch_band_rows<4, 4>(A, B, ld, status, cs.n, C0, st);
-  else if (tpw <= 9)
+  else if (np <= kLuBandResident)
     launch_band_rows<9, 4>(A, B, ld, status, cs.n, C0, st);
   else
-    launch_band_rows<20, 3>(A, B, ld, status, cs.n, C0, st);
+    k_lu_band_rows_long<kLuBandWindow, 4><<<np, kLuThreads, 0, st>>>(A, B.n, (int)ld, B.perm, B.plo, B.cend, status,
+                                                                    B.rowdof, B.coldof, B.scale, B.scale + cs.n, cs.n,
+                                                                    C0);
   launch_coarse_diagonal(cs, B.n, status, st);
   k_coarse_border<<<dim3((cs.n + 255) / 256, cs.n), 256, 0, st>>>(cs.n, cs.fpos, cs.rowptr, cs.val, C0);
 }

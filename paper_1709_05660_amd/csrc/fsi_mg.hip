@@ -798,7 +798,7 @@ static void plan_band(MG &mg, const fsi_csr &J, const std::vector<int> &fpos, hi
   const BandOrder b = band_order(nf, rp, ci, 16);
   const int nslot = (b.window + 15) / 16 * 16;
   // (a singular pattern goes to the chain, whose panels hold every row, and is reported there)
-  if (!b.full || nslot > kLuBandSlots) return;
+  if (!b.full || nslot > kLuBandSlots || !lu_band_reach_ok(b.cend.data(), nf)) return;
   std::vector<int> rpos(J.nrows, -1), cpos(J.nrows, -1), rowdof(nf), coldof(nf);
   for (int f = 0; f < nf; ++f) {
     rpos[dof[f]] = b.rowpos[f];
