@@ -46,6 +46,14 @@ struct alignas(16) Quad {
   T v[4];
 };
 
+// Between one lane's LDS access and another lane's of the same wave.  The
+// hardware keeps a wave's LDS operations in order; this keeps the compiler's
+// (no instruction).
+__device__ __forceinline__ void lu_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // the pivot row (lane ll, register row ql) into scalars
 template <typename T, int R, int NC, int Q = 0>
 __device__ __forceinline__ void lu_take(const T (&v)[R][NC], int ql, int ll, T (&prow)[NC]) {
@@ -187,6 +195,7 @@ __device__ __forceinline__ int lu_columns(T *P, int c0, int (&step)[R], const Lu
   }
   int fail = 0;
   lu_steps<T, R, NC, 0>(v, step, c0, L.scale(), fail);
+  lu_wave_sync();   // lane 0's reciprocals
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const bool pivot = step[q] >= c0 && step[q] < c0 + NC;
@@ -223,9 +232,11 @@ __device__ __forceinline__ void lu_cross(T *P, int c0, int nrt, const LuLds<T, P
     const T x = P[slots[KK * kq + kk] * LS + jl];
     bx[kk] = other ? x : (T)0;
   }
+  lu_wave_sync();   // every lane has its part of the pivot rows
 #pragma unroll
   for (int t = 0; t < NC; t += 4)
     if (other) P[slots[t + kq] * LS + jl] = 0;
+  lu_wave_sync();
   for (int rt = 0; rt < nrt; ++rt) {
     const T *a = P + (rt * 16 + jl) * LS + c0 + KK * kq;
     acc c;
@@ -270,6 +281,7 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
     step[q] = taken || one ? -1 : kLuNb;
   }
   if (lane < kLuNb) L.slots()[lane] = 0;
+  lu_wave_sync();
   int f = 0;
   if constexpr (NC == kLuNb) {
     f = lu_columns<T, R, NC, PB>(P, 0, step, L);
@@ -277,7 +289,9 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
     for (int c0 = 0; c0 < kLuNb; c0 += NC) {
       const int g = lu_columns<T, R, NC, PB>(P, c0, step, L);
       f = f ? f : g;
+      lu_wave_sync();   // the group's rows and pivot slots
       lu_cross<T, NC, PB>(P, c0, (cnt + 15) >> 4, L);
+      lu_wave_sync();
     }
   }
   if (f) return -1 - (p0 + f - 1);
@@ -328,6 +342,7 @@ __device__ __forceinline__ int lu_factor(T *__restrict__ A, int64_t ld, int p, i
       last = base;
       store = kept;
     }
+    if constexpr (!BAND) lu_wave_sync();   // every lane has its row before another takes the slot
     if (store) {
       rown[slot] = occupant;
       if constexpr (PB == 2) {
