@@ -175,23 +175,26 @@ static int64_t footprint(const fsi_level *lv, int nl, const fsi_mg_opts &mo,
                          const fsi_krylov_opts &ko, int64_t *transient_out) {
   const bool mixed = mo.precision != FSI_PREC_FP64;
   const int wbytes = mo.precision == FSI_PREC_FP64 ? 8 : (mo.precision == FSI_PREC_MIXED_FP32 ? 4 : 2);
-  int64_t res = 0, transient = 0;
+  int64_t res = 0, transient = 0, scaled = 0;
   for (int l = 0; l < nl; ++l) {
     const int64_t n = lv[l].J.nrows;
     auto csr = [&](const fsi_csr &A) { return (A.nrows + 1) * 4 + A.nnz * (4 + 8 + (mixed ? 4 : 0)); };
-    res += csr(lv[l].J) + 6 * n * 8;
+    res += csr(lv[l].J) + 6 * n * 8;   // operator, vectors, the rows' exponents
     if (l == 0) {
-      res += n * n * 8;
+      // the inverse, and the banded order: positions, ordered dofs, pivot rows,
+      // (kEquilSteps + 1) exponents a dof and three ints a panel of 16
+      res += n * n * 8 + n * 4 * (5 + kEquilSteps + 1) + (n + 15) / 16 * 12;
       transient = std::max<int64_t>(transient, n * ((n + 15) / 16 * 16) * 8 + 2 * n * 8);
       continue;
     }
+    scaled = std::max<int64_t>(scaled, lv[l].J.nnz);
     res += csr(lv[l].P) + csr(lv[l].R);
     const fsi_patches &P = lv[l].patches;
     // solid blocks apart (solid_precision / refine_sweeps): FP32 owned rows,
     // or full FP32 inverses plus their local block rows
     const bool split = mixed && ((mo.solid_precision != -1 && mo.solid_precision != mo.precision) ||
                                  mo.refine_sweeps > 0);
-    int64_t om = 0, m2 = 0, slots = 0, solid_bytes = 0, mlarge = 0;
+    int64_t om = 0, block_entries = 0, slots = 0, solid_bytes = 0, mlarge = 0;
     for (int k = 0; k < P.npatch; ++k) {
       const int64_t m = P.ptr[k + 1] - P.ptr[k];
       if (m > kMaxPatch) mlarge = std::max(mlarge, m);
@@ -205,16 +208,18 @@ static int64_t footprint(const fsi_level *lv, int nl, const fsi_mg_opts &mo,
         solid_bytes += mo.refine_sweeps > 0 ? m * m * 4 + ks * 8 + (m + 1) * 4 : o * m * 4;
       else
         om += o * m;
-      m2 += m * m;
+      block_entries += (m * block_ld((int)m) + 15) / 16 * 16;   // rows padded to whole tiles
     }
     res += om * wbytes + solid_bytes + P.ptr[P.npatch] * 48;
     // all levels' dense blocks share one setup scratch; the extraction map
     // (two ints per slot, an offset per block row) is setup scratch too
-    transient += m2 * 8 + slots * 8 + P.ptr[P.npatch] * 8;
+    transient += block_entries * 8 + slots * 8 + P.ptr[P.npatch] * 8;
     // blocks above kMaxPatch dofs: the Gauss-Jordan chain's padded working
     // copy and (mixed forms) the FP64 inverse before its cast
     if (mlarge) res += mlarge * ((mlarge + 15) / 16 * 16) * 8 + (mixed ? mlarge * mlarge * 8 : 0) + mlarge * 12;
   }
+  // one level's scaled operator values while its blocks are extracted
+  transient += scaled * (mixed ? 4 : 8);
   // Krylov: V (m+1 columns), Z (m), w, b and x; H and the rotations; the
   // reductions' chunk sums (two sets of kMaxKrylovCols columns) and norms
   const int64_t nf = lv[nl - 1].J.nrows, m = ko.restart;
