@@ -2364,8 +2364,11 @@ int autotune(MG &mg, const char *db_path, hipStream_t st) {
     char key[256], gkey[256];
     int64_t sum_m2 = 0;
     for (const Level &L : mg.lv) sum_m2 += L.sum_m2;
-    snprintf(key, sizeof key, "gj3:%s%d:%d:%lld", mg.mixed ? "f32:" : "", mg.mmax_all, mg.npatch_all,
+    // ":lu": chosen among the Gauss-Jordan variants and the LU; an entry of a
+    // database from before the LU (the same key without it) is measured anew
+    snprintf(key, sizeof key, "gj3:%s%d:%d:%lld:lu", mg.mixed ? "f32:" : "", mg.mmax_all, mg.npatch_all,
              (long long)sum_m2);
+    const std::string before(key, strlen(key) - 3);
     auto gj_key = [&](int var) {
       snprintf(gkey, sizeof gkey, "gjg:%s%d:%d:%lld:%d", mg.mixed ? "f32:" : "", mg.mmax_all,
                mg.npatch_all, (long long)sum_m2, var);
@@ -2444,6 +2447,7 @@ int autotune(MG &mg, const char *db_path, hipStream_t st) {
       }
       mg.gj_variant = best_var;
       set_gj_grid(mg, best_grid, st);
+      db.erase(before);
       db[key] = best_var;
       db[gj_key(best_var)] = best_grid;
       ++measured;
