@@ -165,7 +165,7 @@ struct BandView {
 };
 constexpr int kEquilSteps = 4;
 constexpr int kLuBandSlots = 384;    // waiting rows at most (six a lane of the factoring wave)
-constexpr int kLuBandMax = 2560;     // largest ordered block
+constexpr int kLuBandMax = kMaxCoarse;   // largest ordered block
 constexpr int kLuBandWindow = 8;     // tiles a wave in registers in k_lu_band_rows_long
 // whether the inverse's rows can be found from factors whose panels' columns
 // end at cend (in k_lu_band_rows_long a panel updates tiles in registers only)

@@ -778,11 +778,10 @@ static void pack_level(MG &mg, Level &L, hipStream_t st) {
 }
 // A banded order of the coarsest operator's free block, when there is one
 // that the banded elimination takes (at most kLuBandSlots rows waiting for a
-// pivot at a time).  Then one wave finds the pivots with the waiting rows in
-// its registers, where the chain's pivot steps go over every row of the
-// block with a workgroup barrier each.  Measured, free dofs of a 16x4 (1,074,
-// 125 rows waiting) and a 24x6 coarsest mesh (2,522, 181 rows): 0.98 and
-// 4.4 ms, by the chain 2.5 and 11.2 ms.
+// pivot at a time) and in which it is the faster one (band_time): one wave
+// finds the pivots with the waiting rows in its registers, where the chain's
+// pivot steps go over every row of the block with a workgroup barrier each,
+// but one workgroup does all updates.
 static void plan_band(MG &mg, const fsi_csr &J, const std::vector<int> &fpos, hipStream_t st) {
   const int nf = mg.coarse_nf;
   if (nf == 0 || nf > kLuBandMax) return;
@@ -798,7 +797,8 @@ static void plan_band(MG &mg, const fsi_csr &J, const std::vector<int> &fpos, hi
   const BandOrder b = band_order(nf, rp, ci, 16);
   const int nslot = (b.window + 15) / 16 * 16;
   // (a singular pattern goes to the chain, whose panels hold every row, and is reported there)
-  if (!b.full || nslot > kLuBandSlots || !lu_band_reach_ok(b.cend.data(), nf)) return;
+  if (!b.full || nslot > kLuBandSlots || !lu_band_reach_ok(b.cend.data(), nf) || band_time(b, nf) > chain_time(nf))
+    return;
   std::vector<int> rpos(J.nrows, -1), cpos(J.nrows, -1), rowdof(nf), coldof(nf);
   for (int f = 0; f < nf; ++f) {
     rpos[dof[f]] = b.rowpos[f];

@@ -139,4 +139,19 @@ BandOrder band_order(int n, const std::vector<int64_t> &rowptr, const std::vecto
   return best;
 }
 
+double band_time(const BandOrder &b, int n) {
+  double rows = 0, entries = 0;
+  const int np = (int)b.hi.size();
+  for (int p = 0; p < np; ++p) {
+    const double wait = b.hi[p] - 16 * p;
+    rows += wait;
+    entries += wait * std::max(b.cend[p] - std::min(16 * (p + 1), n), 0);
+  }
+  return 110 + 3.2 * np + 0.077 * rows + 3.2e-4 * entries;
+}
+
+double chain_time(int n) {
+  return n <= 1536 ? 60 + (n + 15) / 16 * (20 + n / 60.0) : 60 + (n + 7) / 8 * (10 + n / 96.0);
+}
+
 }  // namespace fsi

@@ -27,7 +27,7 @@ int main() {
   for (auto &v : rp) { int x; if (scanf("%d", &x) != 1) return 1; v = x; }
   for (auto &v : ci) if (scanf("%d", &v) != 1) return 1;
   const fsi::BandOrder b = fsi::band_order(n, rp, ci, 16);
-  printf("%d %d\\n", b.window, (int)b.full);
+  printf("%d %d %.17g %.17g\\n", b.window, (int)b.full, fsi::band_time(b, n), fsi::chain_time(n));
   line(b.colpos); line(b.rowpos); line(b.hi); line(b.cend);
 }
 """
@@ -46,8 +46,8 @@ def order(tmp_path_factory):
         A.sort_indices()
         text = " ".join(map(str, [A.shape[0], A.nnz, *A.indptr, *A.indices]))
         out = subprocess.run([exe], input=text, check=True, capture_output=True, text=True).stdout.splitlines()
-        window, full = map(int, out[0].split())
-        return (window, bool(full), *(np.array(x.split(), int) for x in out[1:]))
+        window, full, *run.times = map(float, out[0].split())
+        return (int(window), bool(full), *(np.array(x.split(), int) for x in out[1:]))
 
     return run
 
@@ -90,3 +90,29 @@ def test_orders_of_banded_patterns(order, n, half):
         lo, up = 16 * k, min(16 * (k + 1), n)
         assert not B[hi[k]:, :up].any() and not B[:hi[k], cend[k]:].any()
         assert lo < hi[k] <= lo + window
+
+
+# measured on the device (us): the banded elimination and the Gauss-Jordan chain
+@pytest.mark.parametrize("mesh,transient,band,chain", [
+    ((16, 4), False, 980, 2600), ((24, 6), False, 3622, 11029), ((24, 8), True, 7130, 21144),
+    ((8, 8), False, 2944, 2732), ((8, 6), True, 1335, 1780), ((8, 2, 2), False, 1427, 2149),
+    ((8, 2, 4), False, 11953, 9082), ((10, 4, 2), True, 15867, 13527), (120, None, 190, 237), (384, None, 941, 681)])
+def test_the_faster_inverse_is_chosen(order, mesh, transient, band, chain):
+    """The builder's coarsest operators of these meshes (their free block), and dense ones."""
+    if transient is None:
+        A = np.ones((mesh, mesh))
+    else:
+        from paper_1709_05660_amd import Problem
+        from synth import ProblemSpec, fourier_coefficients
+        dim = len(mesh)
+        s = ProblemSpec(dim=dim, nx=2 * mesh[0], ny=2 * mesh[1], nz=2 * mesh[2] if dim == 3 else 1, levels=2, patch=2,
+                        lx=(0.25 if dim == 2 else 0.5) * mesh[0], transient=transient, seed=3)
+        rp, ci, v, shape = Problem(s, fourier_coefficients(dim, 3)).csr(0)
+        P = sp.csr_matrix((np.ones(len(ci)), ci, rp), shape=shape)
+        free = ~((np.diff(P.indptr) == 1) & (np.diff(P.tocsc().indptr) == 1))
+        A = P[free][:, free]
+    window = order(A)[0]
+    est_band, est_chain = order.times
+    print(mesh, "window", window, "estimates", est_band, est_chain, "measured", band, chain)
+    assert (est_band > est_chain) == (band > chain)
+    assert abs(est_band / band - 1) < 0.15 and abs(est_chain / chain - 1) < 0.15

@@ -27,8 +27,9 @@ def equilibrated(A):
     return 2.0 ** r, 2.0 ** c
 
 
-# 1,674 to 2,522 free dofs (105 to 158 panels)
+# 1,674 to 3,426 free dofs (105 to 215 panels)
 @pytest.mark.parametrize("dim,mesh,transient", [(2, (24, 6), False), (2, (24, 6), True), (2, (16, 6), False),
+                                                (2, (24, 8), True),
                                                 (3, (16, 2, 2), True)])
 def test_long_coarsest_operator_against_lapack(dim, mesh, transient):
     import torch
