@@ -204,6 +204,7 @@ struct MG {
   int *lu_order = nullptr;     // the blocks of the batched inversions, largest first (lu_nblk)
   double *scaled_val = nullptr;   // a level's scaled operator values while its blocks are extracted (setup scratch)
   int lu_nblk = 0;
+  bool gj_beside_chain = false;   // Gauss-Jordan for the blocks, for the coarsest chain's sake
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipGraphExec_t coarse_graph = nullptr;   // the coarsest inversion's launch chain, replayed per refactor

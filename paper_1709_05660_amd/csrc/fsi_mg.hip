@@ -797,8 +797,11 @@ static void plan_band(MG &mg, const fsi_csr &J, const std::vector<int> &fpos, hi
   const BandOrder b = band_order(nf, rp, ci, 16);
   const int nslot = (b.window + 15) / 16 * 16;
   // (a singular pattern goes to the chain, whose panels hold every row, and is reported there)
-  if (!b.full || nslot > kLuBandSlots || !lu_band_reach_ok(b.cend.data(), nf) || band_time(b, nf) > chain_time(nf))
-    return;
+  if (!b.full || nslot > kLuBandSlots || !lu_band_reach_ok(b.cend.data(), nf)) return;
+  // (beside blocks the chain shares the device with them, the elimination has
+  // its own compute unit: 8x8, 2.94 ms alone against 2.73, a step with 320
+  // blocks 4.68 against 4.77)
+  if (band_time(b, nf) > (mg.npatch_all ? 1.1 : 1.0) * chain_time(nf)) return;
   std::vector<int> rpos(J.nrows, -1), cpos(J.nrows, -1), rowdof(nf), coldof(nf);
   for (int f = 0; f < nf; ++f) {
     rpos[dof[f]] = b.rowpos[f];
@@ -923,7 +926,23 @@ static bool lu_possible(const MG &mg) {
   return mg.large.empty() && mg.lu_nblk > 0;
 }
 static bool lu_chosen(const MG &mg) {
-  return lu_possible(mg) && (mg.gj_variant == kGjAuto || mg.gj_variant == kLu64 || mg.gj_variant == kLu32);
+  if (!lu_possible(mg)) return false;
+  return mg.gj_variant == kGjAuto ? !mg.gj_beside_chain : mg.gj_variant == kLu64 || mg.gj_variant == kLu32;
+}
+// Beside the chain of a coarsest operator that is not eliminated in a banded
+// order, one or two rounds of blocks stay with Gauss-Jordan unless it takes far
+// longer than the chain: the LU moves the same bytes in a third of the time and
+// takes compute units and bandwidth from the chain's updates.  64 blocks of 632
+// dofs beside the chain of 8x2x4, FP64: a refactor by LU 9.9 ms, Gauss-Jordan
+// 9.3 (12.2 and 15.7 for a handle whose two streams fell on one hardware queue,
+// one in six); 80 of 372 beside that of 8x8 2.89, 2.80; a step with 336 of 372
+// 8.06, 7.25; one with 1,344 of 112 (FP32), six rounds, 5.7, 6.0.  The estimate
+// of a round, 3 + m / 100 us a column, is above the measured 1.4 ms at 372 and
+// 2.7 at 490, and 5.9 ms at 632 (4.2 in FP32, 6.3 in FP64).
+static bool gauss_jordan_beside_chain(const MG &mg) {
+  if (mg.coarse_nf == 0 || mg.band.nslot || mg.npatch_all == 0) return false;
+  const int grid = gj_batched_grid(mg.npatch_all), rounds = (mg.npatch_all + grid - 1) / grid;
+  return rounds <= 2 && rounds * mg.mmax_all * (3 + mg.mmax_all / 100.0) <= 2 * chain_time(mg.coarse_nf);
 }
 
 // factors every block in place and writes the rows that the V-cycle uses
@@ -1803,6 +1822,7 @@ MG *mg_setup(const fsi_level *levels, int nlevels, const fsi_mg_opts *opts, hipS
       mg->coarse_fpos = dupload(fpos.data(), n0, mg->owned, st);
       mg->coarse_dlist = dupload(dlist.data(), (int64_t)dlist.size(), mg->owned, st);
       plan_band(*mg, J0, fpos, st);
+      mg->gj_beside_chain = gauss_jordan_beside_chain(*mg);
     }
     if (!mg->large.empty()) {
       // the chain's working copy: rows padded to a multiple of 16 doubles, + 64 past the end
