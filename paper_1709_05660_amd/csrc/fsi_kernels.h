@@ -164,7 +164,9 @@ struct BandView {
   int *perm = nullptr, *plo = nullptr, *scale = nullptr;
 };
 constexpr int kEquilSteps = 4;
-constexpr int kLuBandSlots = 384;    // waiting rows at most (six a lane of the factoring wave)
+// waiting rows at most, six a lane of the factoring wave (with eight, 8x2x4 and
+// 10x4x2 coarsest meshes took 12.0 and 15.9 ms, by the chain 9.1 and 13.5)
+constexpr int kLuBandSlots = 384;
 constexpr int kLuBandMax = kMaxCoarse;   // largest ordered block
 constexpr int kLuBandWindow = 8;     // tiles a wave in registers in k_lu_band_rows_long
 // whether the inverse's rows can be found from factors whose panels' columns
