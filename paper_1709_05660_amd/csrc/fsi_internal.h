@@ -195,7 +195,7 @@ struct MG {
   // diagonal-only dofs by a reciprocal
   int coarse_nf = 0, coarse_nd = 0;
   int *coarse_fpos = nullptr, *coarse_dlist = nullptr;
-  BandView band;   // its free block in a banded order (nslot 0: none that the banded elimination takes)
+  BandView band;   // its free block in a banded order (nslot 0: left to the Gauss-Jordan chain)
   int npatch_all = 0, mmax_all = 1;
   int gj_variant = 0;     // batched Gauss-Jordan kernel variant (GjVariant, 0 = by size)
   int gj_grid = 0;        // its workgroups, and their block lists (gj_schedule)
